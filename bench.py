@@ -38,7 +38,10 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-KERNEL_SRC = os.path.join(ROOT, "paper_2103_14990_amd", "csrc", "batch_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_2103_14990_amd", "csrc")
+# kernels behind the three timed launches when the engine iterates through the global recursions
+GLOBAL_KERNELS = {"bphi_kernel": "bsim_fwd_kernel", "bpsi_kernel": "bsim_adj_kernel + bstep_kernel",
+                  "bdecide_kernel": "bgather_kernel"}
 
 
 def log(*a):
@@ -47,9 +50,14 @@ def log(*a):
 
 def kernel_source_hash(kernel: str) -> str:
     """sha256 (first 16 hex) of the kernel's own source text: from the template line before its
-    definition to the next section marker of batch_kernels.hip."""
-    src = open(KERNEL_SRC).read()
-    at = src.index(f" void {kernel}(")
+    definition to the next section marker of its source file."""
+    for name in ("batch_kernels.hip", "batch_global.h"):
+        src = open(os.path.join(CSRC, name)).read()
+        at = src.find(f" void {kernel}(")
+        if at < 0:  # a launch-bounds attribute between the return type and the name
+            at = src.find(f" {kernel}(BArgs")
+        if at >= 0:
+            break
     start = src.rfind("\ntemplate", 0, at) + 1
     end = src.find("\n// ------", at)
     return hashlib.sha256(src[start:end if end > 0 else len(src)].encode()).hexdigest()[:16]
@@ -62,8 +70,19 @@ def batch_algorithmic_bytes(info: dict, n_sub: int, rs: int, B: int, basis_bytes
     tau / eta / W (bf16 hi + lo) over sum_j k_j coordinates, per instance.
     bpsi_kernel: bases + alpha (read) + tau, eta (read, write) + W (write) + row-subsystem sums.
     bphi_kernel: bases + W (read) + alpha_prev, b (read), alpha, s (write) + w, lb, ub.
+    Through the global recursions (info batch_global): the first launch reads alpha_prev, the input
+    rows of b and U, writes alpha and s; the second reads alpha and the input rows of the bases once,
+    tau and eta (read, write), g (write, read), writes every tile's share of U; the third reads the
+    shares and writes U.
     """
     dk, sk, R = info["sum_dcol_k"], info["sum_k"], n_sub * rs
+    if info["batch_global"] and basis_bytes == 4:
+        nu_t = info["input_rows"]  # input rows per subsystem
+        share = 4 * info["n_tiles"] * nu_t * B
+        fwd = 12 * B * R + 12 * R + 8 * B * n_sub * nu_t
+        step = 4 * B * R + 4 * info["sum_du_k"] + 16 * B * sk + 8 * B * n_sub * nu_t + share
+        gather = share + 4 * B * n_sub * nu_t
+        return {"bphi_kernel": fwd, "bpsi_kernel": step, "bdecide_kernel": gather, "iteration": fwd + step + gather}
     nb = basis_bytes * dk
     bpsi = nb + 4 * B * R + 16 * B * sk + 4 * B * sk + 8 * B * n_sub
     bphi = nb + 4 * B * sk + 16 * B * R + 12 * R + 8 * B * n_sub
@@ -703,7 +722,7 @@ def main() -> int:
         s16, e16 = timed_batches(p16, u16)
         s32, e32 = timed_batches(p32, u32)
         k16 = p16.time_batch_kernels(B, xl.data_ptr(), 20)
-        ab16 = batch_algorithmic_bytes(pr.info, N, rs, B, basis_bytes=2)
+        ab16 = batch_algorithmic_bytes(p16.info, N, rs, B, basis_bytes=2)
         tier = {"eps": eps_t, "instances": nl, "start": "cold",
                 "time_to_eps_ms": round(1e3 * e16 / nl, 4),
                 "iters_mean": float(np.mean([q["iters"] for q in s16])),
@@ -771,20 +790,25 @@ def main() -> int:
         log(f"mixed networks: {mixed}")
 
     # ---- roofline of the dominant batched kernel (HIP events around each launch)
-    ab = batch_algorithmic_bytes(pr.info, N, rs, B)
+    glob = bool(pr.info["batch_global"])
+    ab = batch_algorithmic_bytes({**pr.info, "input_rows": net.nu * (wl.T - 1)}, N, rs, B)
     ku = pr.time_batch_kernels(B, x0[args.warmup].data_ptr(), 20)
     kname = max(ku, key=ku.get)
-    per_kernel = {k: {"us": round(v, 2), "GB/s": round(ab[k] / (v * 1e-6) / 1e9, 1) if ab[k] else None}
+    per_kernel = {GLOBAL_KERNELS[k] if glob else k:
+                  {"us": round(v, 2), "GB/s": round(ab[k] / (v * 1e-6) / 1e9, 1) if ab[k] else None}
                   for k, v in ku.items()}
     achieved = ab[kname] / (ku[kname] * 1e-6) / 1e9
-    roofline = {"bound": "hbm", "kernel": kname, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+    kshow = GLOBAL_KERNELS[kname] if glob else kname
+    roofline = {"bound": "hbm", "kernel": kshow, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "avg_launch_us": round(ku[kname], 2), "algorithmic_bytes_per_launch": int(ab[kname]),
                 "instances_per_launch": B, "per_kernel": per_kernel,
                 "iteration_us": round(sum(ku.values()), 2),
-                "traffic": traffic_record(args.workload, kname, ab[kname])}
-    # matrix-core use of the dominant kernel: three bf16 products of 2 sum_j D_col k_j B flops
-    mfma_tf = 3 * 2.0 * pr.info["sum_dcol_k"] * B / (ku[kname] * 1e-6) / 1e12
+                "traffic": traffic_record(args.workload, kshow.split()[-1], ab[kname])}
+    # matrix-core use of the dominant kernel: three bf16 products of 2 sum_j D_col k_j B flops (through
+    # the global recursions: both products of the iteration, with the input rows)
+    prod = 2 * pr.info["sum_du_k"] if glob else pr.info["sum_dcol_k"]
+    mfma_tf = 3 * 2.0 * prod * B / (ku[kname] * 1e-6) / 1e12
     roofline["mfma"] = {"achieved_tflops": round(mfma_tf, 1), "peak_tflops_bf16": 2500.0,
                         "frac": round(mfma_tf / 2500.0, 4)}
 

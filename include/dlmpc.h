@@ -82,8 +82,10 @@ typedef enum {
                                        device kernels (host-only problems always do) */
 #define DLMPC_FLAG_NO_TUNE 0x20u   /* no autotuning at setup: graph schedule (unless the persistent
                                       one is asked for), batched-engine kernel variants at their
-                                      defaults (1 instance tile per Phi-comp wave, Psi-comp split at
-                                      8x the mean basis cost); the tuning cache is not used */
+                                      defaults (the global recursions where the problem allows them,
+                                      dlmpc_info.batch_global; for the dense products 1 instance tile
+                                      per Phi-comp wave, Psi-comp split at 8x the mean basis cost);
+                                      the tuning cache is not used */
 #define DLMPC_FLAG_NO_CHECK 0x10u  /* skip the FP64 check of the stopping iterate that every solve
                                       otherwise runs (stats kkt, eq_resid, u0_check are then 0) */
 /* Per-iteration schedules of single-instance solves, the designs of Section III that this
@@ -247,7 +249,12 @@ typedef struct {
    * by the flag, or by timing at setup when no schedule flag is given (tune_structured_us: its
    * per-iteration time on the graph schedule, 0 if not timed). */
   int32_t psi_structured;
-  int32_t pad_info;
+  int32_t batch_global; /* 1 if the batched engine iterates through the global recursions of the plant (the
+                           forward and adjoint recursions of A once per instance, products with the
+                           input rows of the null bases only), 0 if through the dense products.
+                           Chosen by timing at setup; not available in DLMPC_FP32_BF16, for networks
+                           of more than 4096 states, for patches beyond on-chip staging, and for
+                           plants whose A^t grows by more than 32 over the horizon */
   double tune_structured_us;
   int64_t sum_du_k;     /* sum over subsystems of mu_j * k_j, mu_j = p_j * nu * (T - 1) the input
                            rows of column block j (entries of the structured Psi-comp's bases N_u) */
@@ -324,7 +331,11 @@ int dlmpc_time_kernels(struct dlmpc_problem *p, const double *x0_dev, int32_t it
  * [B][N*nx] (device), started from row multipliers alpha0 = 0 (DLMPC_START_ALPHA, so that
  * every iteration runs the full products) without early stop; `iters` iterations with each
  * kernel launched on its own between HIP events on the problem's stream.
- * us_per_launch gets the mean device time per launch of, in this order, the batched Phi-comp
+ * us_per_launch gets the mean device time per launch of the three steps of an iteration. With
+ * the global recursions (dlmpc_info.batch_global): the forward recursion with the row update
+ * (bsim_fwd_kernel); the adjoint recursion and the products with the input rows, with Lambda and
+ * Conv terms (bsim_adj_kernel + bstep_kernel); the sum of the products and the stopping decision
+ * (bgather_kernel). With the dense products: the batched Phi-comp
  * (bphi_kernel: row solves of all instances, products with the null bases on the matrix
  * cores), the batched Psi-comp with Lambda and Conv terms (bpsi_kernel) and the per-instance
  * stopping decision (bdecide_kernel). The batched state is left unspecified. */

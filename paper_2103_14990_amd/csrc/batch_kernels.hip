@@ -94,6 +94,19 @@ __device__ __forceinline__ T wsum(T v) {
   return v;
 }
 
+// Element (b, m, l) of the row vectors alpha and s, and the subsystem and local row of their e-th
+// element in storage order (instances aside).
+__device__ __forceinline__ int64_t row_at(const BArgs &a, int b, int m, int l) {
+  return b * a.rb + m * a.rm + l * a.rl;
+}
+__device__ __forceinline__ void row_decode(const BArgs &a, int64_t e, int &m, int &l) {
+  const int d = a.glob ? a.N : a.rs, q = int(e / d), r = int(e - int64_t(q) * d);
+  m = a.glob ? r : q;
+  l = a.glob ? q : r;
+}
+
+#include "batch_global.h"
+
 // ------------------------------------------------------------------ per-solve precompute
 
 // Instances per bprecompute_kernel block, and the parts one instance's row sweeps are split
@@ -152,8 +165,21 @@ __global__ __launch_bounds__(256) void bprecompute_kernel(BArgs a, const double 
     a.nrm[int64_t(b) * a.N + m] = static_cast<float>(sn);
   }
   const int64_t plane = int64_t(a.Bmax) * a.N * rs;
+  if (a.glob) {  // input rows of b only: its state rows follow by the plant; alpha needs no clearing
+    const int nxT = NX * a.T, nuT = rs - nxT;
+    for (int e = tid; e < nuT * ny; e += 256) {
+      const int yy = e / nuT, l = e - yy * nuT;
+      double bv = 0.0;
+      for (int q = 0; q < np; ++q) {
+        const float *o = a.off + s_base[q] + nxT + l;
+#pragma unroll
+        for (int c = 0; c < NX; ++c) bv += s_x[yy][q][c] * double(o[int64_t(c) * s_ld[q]]);
+      }
+      a.bu[(int64_t(s_b[yy]) * a.N + m) * nuT + l] = static_cast<float>(bv);
+    }
+  }
   // row l of m for instance yy (instances fastest: neighbouring slots share a row's cache line)
-  for (int e = tid; e < rs * ny; e += 256) {
+  for (int e = a.glob ? rs * ny : tid; e < rs * ny; e += 256) {
     const int l = e / ny, yy = e - l * ny;
     const int64_t ri = (int64_t(m) * rs + l) * a.Bmax + s_b[yy];  // row vectors: [R][Bmax]
     double bv = 0.0;
@@ -167,7 +193,8 @@ __global__ __launch_bounds__(256) void bprecompute_kernel(BArgs a, const double 
     a.alpha[plane + ri] = 0.f;
     a.s[ri] = 0.f;
   }
-  const int64_t k0 = a.koff[m], nk = a.koff[m + 1] - k0;
+  // (through the global recursions a cold iteration 2 and a join's start read neither tau nor eta)
+  const int64_t k0 = a.koff[m], nk = (a.glob && (!warm || join)) ? 0 : a.koff[m + 1] - k0;
   for (int64_t e = tid; e < nk * ny; e += 256) {
     const int64_t i = k0 + e / ny;
     const int b = s_b[int(e % ny)];
@@ -202,6 +229,8 @@ __global__ __launch_bounds__(256) void bprecompute_kernel(BArgs a, const double 
       c->last_rp = c->last_rd = INFINITY;
       c->batch = B;
       c->warm = warm;
+      c->rp_bits = c->rd_bits = 0ull;
+      c->done_count = c->n_stop = 0u;
     }
   }
 }
@@ -226,7 +255,7 @@ __global__ __launch_bounds__(64) void bpart_sum_kernel(BArgs a, const int32_t *s
 __global__ __launch_bounds__(256) void bwarm_alpha_kernel(BArgs a, const double *alpha0, int B) {
   const int64_t ny = int64_t(a.N) * a.rs;
   for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < int64_t(B) * ny; i += int64_t(gridDim.x) * 256)
-    a.alpha[(i % ny) * a.Bmax + i / ny] = static_cast<float>(alpha0[i]);
+    a.alpha[row_at(a, int(i / ny), int(i % ny) / a.rs, int(i % ny) % a.rs)] = static_cast<float>(alpha0[i]);
 }
 
 __global__ __launch_bounds__(256) void bexport_alpha_kernel(BArgs a, double *out, int B) {
@@ -235,7 +264,8 @@ __global__ __launch_bounds__(256) void bexport_alpha_kernel(BArgs a, double *out
   for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < int64_t(B) * ny; i += int64_t(gridDim.x) * 256) {
     const int b = int(i / ny);
     const int p = a.ictl[b].iters & 1;  // the plane the stopping iteration wrote
-    out[i] = double(a.alpha[p * plane + (i - int64_t(b) * ny) * a.Bmax + b]);
+    const int r = int(i - int64_t(b) * ny);
+    out[i] = double(a.alpha[p * plane + row_at(a, b, r / a.rs, r % a.rs)]);
   }
 }
 
@@ -906,16 +936,20 @@ __global__ __launch_bounds__(256) void boutput_kernel(BArgs a, double *u0, const
   const int64_t orow = dst ? dst[blockIdx.x] : blockIdx.x;
   const int64_t ny = int64_t(a.N) * a.rs, chunk = (ny + kParts - 1) / kParts;
   const int64_t r0 = part * chunk, r1 = min(ny, r0 + chunk);
-  const float *sb = a.s + b;  // row i of instance b at sb[i * Bmax]
   double acc = 0.0;
-  for (int64_t i = r0 + tid; i < r1; i += 256) acc += a.w64[i] * double(sb[i * a.Bmax]) * double(sb[i * a.Bmax]);
+  for (int64_t i = r0 + tid; i < r1; i += 256) {
+    int m, l;
+    row_decode(a, i, m, l);
+    const double y = double(a.s[row_at(a, b, m, l)]);
+    acc += a.w64[int64_t(m) * a.rs + l] * y * y;
+  }
   acc = wsum(acc);
   if ((tid & 63) == 0) red[tid >> 6] = acc;
   __syncthreads();
   if (tid == 0) a.bpart[(int64_t(b) * 2 + 1) * kParts + part] = (red[0] + red[1]) + (red[2] + red[3]);
   for (int i = part * 256 + tid; i < a.N * a.nu; i += kParts * 256) {
     const int m = i / a.nu, q = i - m * a.nu;
-    u0[orow * a.N * a.nu + i] = double(sb[(int64_t(m) * a.rs + NX * a.T + q) * a.Bmax]);
+    u0[orow * a.N * a.nu + i] = double(a.s[row_at(a, b, m, NX * a.T + q)]);
   }
 }
 
@@ -1099,7 +1133,7 @@ __global__ __launch_bounds__(256) void bcheck_y_kernel(BArgs a, const double *x0
           nr += xc * xc;
         }
       }
-      const int64_t rb = (int64_t(m) * rs + l) * a.Bmax + c.b;
+      const int64_t rb = row_at(a, c.b, m, l);
       const double apv = a.alpha[(c.cur ? 0 : plane) + rb], acv = a.alpha[(c.cur ? plane : 0) + rb];
       a.y64[int64_t(c.b) * a.N * rs + int64_t(m) * rs + l] = ((c.coef * bsum + acc[nt][v]) - nr * apv) + nr * acv;
     }
@@ -1151,8 +1185,7 @@ __global__ __launch_bounds__(256) void bcheck_red_kernel(BArgs a, const double *
       jv += a.w64[o] * yv * yv;
     }
     for (int q = 0; q < nu; ++q) {
-      const int64_t o = int64_t(m) * rs + NX * T + q;
-      ud = fmax(ud, fabs(double(a.s[o * a.Bmax + b]) - ym[NX * T + q]));
+      ud = fmax(ud, fabs(double(a.s[row_at(a, b, m, NX * T + q)]) - ym[NX * T + q]));
     }
   }
 #pragma unroll
@@ -1273,11 +1306,21 @@ __global__ __launch_bounds__(256) void bstash_kernel(BArgs a, BArgs st, const in
   }
   __syncthreads();
   const int64_t R = int64_t(a.N) * a.rs, plane = R * a.Bmax, eplane = a.ktot * a.Bmax;
-  const int64_t e = blockIdx.x * 256ll + threadIdx.x, r = e / S;
-  const int y = int(e - r * S);
+  const int64_t e = blockIdx.x * 256ll + threadIdx.x;
   if (e < S) st.ictl[s_t[e]] = a.ictl[s_f[e]];
+  int64_t r = e / S;
+  int y = int(e - r * S);
+  if (a.glob && e < R * S) {  // row vectors instance by instance there
+    y = int(e / R);
+    r = e - y * R;
+  }
   const int f = s_f[y], t = s_t[y];
-  if (r < R) {
+  if (r < R && a.glob) {
+    const int64_t of = f * R + r, ot = t * R + r;
+    st.alpha[ot] = a.alpha[of];
+    st.alpha[plane + ot] = a.alpha[plane + of];
+    st.s[ot] = a.s[of];
+  } else if (r < R) {
     const int64_t o = r * a.Bmax;
     st.alpha[o + t] = a.alpha[o + f];
     st.alpha[plane + o + t] = a.alpha[plane + o + f];
@@ -1473,7 +1516,8 @@ __global__ __launch_bounds__(256) void bexport_y_kernel(BArgs a, double *out, in
   const int64_t ny = int64_t(a.N) * a.rs;
   for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
     const int64_t b = i / ny;
-    out[i] = double(a.s[(i - b * ny) * a.Bmax + b]);
+    const int r = int(i - b * ny);
+    out[i] = double(a.s[row_at(a, int(b), r / a.rs, r % a.rs)]);
   }
 }
 
@@ -1568,6 +1612,41 @@ __global__ void bfragu_kernel(const double *__restrict__ nb, const int64_t *__re
 // (splitting blocks of two to four times the mean cost more in partial sums than it gained).
 constexpr int kPsiCaps[] = {2, 4, 8, 16, 1 << 20};
 constexpr int kPsiCapDefault = 8;
+
+// Growth of the plant over the horizon: largest |A^t v|_inf / |v|_inf over t < T and eight fixed sign
+// vectors v (the sum of squares of a row of A^t shows in every one of them). The limit lies where the
+// recursions' rounding begins to cost more than the dense products': relative error of u(0) after 40
+// iterations against FP64, recursions / dense, emulated on random plants: growth 9 1.2e-6 / 2.6e-6, 46
+// 4.4e-6 / 2.8e-6, 93 3.4e-6 / 3.8e-6, 670 4.0e-6 / 1.9e-6, 2700 7.6e-6 / 2.0e-6; the swing networks
+// and the paper's chain, 2 to 15, have 5e-7 / 2e-6.
+constexpr double kMaxGrowth = 32.0;
+constexpr size_t kGlobLds = 150 * 1024;  // on-chip staging of one block (160 KB per CU)
+constexpr size_t kStepLds2 = 71 * 1024;  // two blocks per CU, beside their 9 KB of static LDS
+double global_growth(const HostSetup &hs) {
+  const int N = hs.N, nx = hs.nx;
+  double g = 0.0;
+  for (int v = 0; v < 8; ++v) {
+    std::vector<double> x(size_t(N) * nx), y(size_t(N) * nx);
+    uint64_t h = 0x9e3779b97f4a7c15ull * uint64_t(v + 1);
+    for (auto &e : x) {
+      h = h * 6364136223846793005ull + 1442695040888963407ull;
+      e = (h >> 63) ? 1.0 : -1.0;
+    }
+    for (int t = 1; t < hs.T; ++t) {
+      for (int m = 0; m < N; ++m)
+        for (int c = 0; c < nx; ++c) {
+          double s = 0.0;
+          for (int64_t q = hs.a_rowptr[m]; q < hs.a_rowptr[m + 1]; ++q)
+            for (int c2 = 0; c2 < nx; ++c2)
+              s += hs.a_blocks[size_t(q) * nx * nx + c * nx + c2] * x[size_t(hs.a_colidx[q]) * nx + c2];
+          y[size_t(m) * nx + c] = s;
+          g = std::max(g, std::fabs(s));
+        }
+      x.swap(y);
+    }
+  }
+  return g;
+}
 
 struct PsiSplit {
   std::vector<int32_t> pu_j, pu_r0, pu_r1, pu_p, pj_n, pj_first;
@@ -1907,6 +1986,10 @@ class BatchEngineT final : public BatchEngine {
     a.src_bs = 1;
     a.src_rs = bmax;
     ny_ = int64_t(N) * hs.rs;
+    a.rb = 1;
+    a.rm = int64_t(hs.rs) * bmax;
+    a.rl = bmax;
+    if ((rc = init_global(err))) return rc;
     a.phi_mode = 0;
     a.src = nullptr;
     a.dst_k = nullptr;
@@ -1938,7 +2021,17 @@ class BatchEngineT final : public BatchEngine {
     ia.src_bs = src_bs;
     ia.src_rs = src_rs;
     ia.dst_k = dst_k;
-    launch_psi(ia);
+    if (glob_) {
+      launch_adj(ia);
+      BENG_CHECK(hipGetLastError());
+      launch_step(ia);
+      if (wmode != 0) {  // the shares of this pass's product operand
+        BENG_CHECK(hipGetLastError());
+        launch_gather(ia);
+      }
+    } else {
+      launch_psi(ia);
+    }
     BENG_CHECK(hipGetLastError());
     return DLMPC_OK;
   }
@@ -1946,7 +2039,7 @@ class BatchEngineT final : public BatchEngine {
   int start_alpha(const double *alpha0_dev, std::string &err) override {
     hipLaunchKernelGGL(bwarm_alpha_kernel, dim3(1024), dim3(256), 0, stream_, args_, alpha0_dev, B_);
     BENG_CHECK(hipGetLastError());
-    return project_t(args_.alpha, 1, args_.Bmax, args_.eta, 2, err);  // plane 0: previous iterate of iteration 1
+    return project_t(args_.alpha, args_.rb, args_.rl, args_.eta, 2, err);  // plane 0: previous iterate of iteration 1
   }
 
   int start_trajectory(const double *y0_dev, int cg_iters, std::string &err) override {
@@ -1954,24 +2047,38 @@ class BatchEngineT final : public BatchEngine {
       hipLaunchKernelGGL(btraj_load_kernel, dim3(1024), dim3(256), 0, stream_, args_, y0_dev, B_);
       BENG_CHECK(hipGetLastError());
     }
-    hipLaunchKernelGGL((bsim_kernel<NX>), dim3(B_), dim3(1024), 0, stream_, args_, nullptr);
-    BENG_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(bcg_init_kernel, dim3(B_, kParts), dim3(1024), 0, stream_, args_, nullptr, 0);
-    BENG_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(bpart_sum_kernel, dim3(1), dim3(64), 0, stream_, args_, nullptr, B_, 0);
-    BENG_CHECK(hipGetLastError());
+    int rc;
+    if ((rc = start_vectors(nullptr, B_, 0, err))) return rc;
     BArgs qa = args_;
     qa.phi_mode = 1;
-    int rc;
     for (int k = 0; k < cg_iters; ++k) {
       if ((rc = project_t(args_.cg_p, ny_, 1, args_.eta, 1, err))) return rc;  // eta = N' p, W = ||x0_j||^2 eta
-      launch_phi(qa);  // q = M p
+      if (glob_)
+        launch_fwd(qa);
+      else
+        launch_phi(qa);  // q = M p
       BENG_CHECK(hipGetLastError());
       launch_cg_step(B_, 0);
       BENG_CHECK(hipGetLastError());
     }
     if ((rc = project_t(args_.cg_x, ny_, 1, args_.tau, 0, err))) return rc;  // tau = N' beta
-    return project_t(args_.alpha, 1, args_.Bmax, args_.eta, 2, err);         // eta = N' alpha^0, W
+    return project_t(args_.alpha, args_.rb, args_.rl, args_.eta, 2, err);    // eta = N' alpha^0, W
+  }
+
+  // State rows, CG vectors and alpha^0 of a trajectory start (yhat holds the input rows).
+  int start_vectors(const int32_t *slots, int S, int pl, std::string &err) {
+    if (glob_) {
+      launch_sim_start(slots, S, pl);
+      BENG_CHECK(hipGetLastError());
+      return DLMPC_OK;
+    }
+    hipLaunchKernelGGL((bsim_kernel<NX>), dim3(S), dim3(1024), 0, stream_, args_, slots);
+    BENG_CHECK(hipGetLastError());
+    hipLaunchKernelGGL(bcg_init_kernel, dim3(S, kParts), dim3(1024), 0, stream_, args_, slots, pl);
+    BENG_CHECK(hipGetLastError());
+    hipLaunchKernelGGL(bpart_sum_kernel, dim3(1), dim3(64), 0, stream_, args_, slots, S, 0);
+    BENG_CHECK(hipGetLastError());
+    return DLMPC_OK;
   }
 
   float *yhat() override { return args_.yhat; }
@@ -2008,14 +2115,8 @@ class BatchEngineT final : public BatchEngine {
     BENG_CHECK(hipGetLastError());
     hipLaunchKernelGGL(bscatter_rows_kernel, dim3(S, 16), dim3(256), 0, stream_, ypred, d_slots_, ny_, args_.yhat);
     BENG_CHECK(hipGetLastError());
-    hipLaunchKernelGGL((bsim_kernel<NX>), dim3(S), dim3(1024), 0, stream_, args_, d_slots_);
-    BENG_CHECK(hipGetLastError());
     // the CG steps and the start projections run inside the following iterations (phases)
-    hipLaunchKernelGGL(bcg_init_kernel, dim3(S, kParts), dim3(1024), 0, stream_, args_, d_slots_, -1);
-    BENG_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(bpart_sum_kernel, dim3(1), dim3(64), 0, stream_, args_, d_slots_, S, 0);
-    BENG_CHECK(hipGetLastError());
-    return DLMPC_OK;
+    return start_vectors(d_slots_, S, -1, err);
   }
 
   int output_slots(double *u0_dev, const int32_t *slots, const int32_t *dst, int S, std::string &err) override {
@@ -2053,7 +2154,16 @@ class BatchEngineT final : public BatchEngine {
   }
 
   int launch_one(int k, std::string &err) override {
-    if (k == 0)
+    if (glob_ && k == 0)
+      launch_fwd(args_);
+    else if (glob_ && k == 1) {
+      launch_adj(args_);
+      BENG_CHECK(hipGetLastError());
+      launch_step(args_);
+    }
+    else if (glob_)
+      launch_gather(args_);
+    else if (k == 0)
       launch_phi(args_);
     else if (k == 1)
       launch_psi(args_);
@@ -2064,6 +2174,21 @@ class BatchEngineT final : public BatchEngine {
   }
 
   int iteration(std::string &err, bool joins) override {
+    if (glob_) {
+      launch_fwd(args_);
+      BENG_CHECK(hipGetLastError());
+      if (joins) {  // the CG step of streamed joins sits between q = M p and the next projection
+        launch_cg_step(args_.Bmax, 1);
+        BENG_CHECK(hipGetLastError());
+      }
+      launch_adj(args_);
+      BENG_CHECK(hipGetLastError());
+      launch_step(args_);
+      BENG_CHECK(hipGetLastError());
+      launch_gather(args_);
+      BENG_CHECK(hipGetLastError());
+      return DLMPC_OK;
+    }
     launch_phi(args_);
     BENG_CHECK(hipGetLastError());
     if (joins) {  // CG steps of streamed joins (a no-op for instances in the ADMM iteration)
@@ -2126,6 +2251,25 @@ class BatchEngineT final : public BatchEngine {
     *phi_ntw = phi_ntw_;
     *psi_capx = psi_capx_;
     *n_units = n_units_;
+  }
+
+  bool global_available() const override { return glob_ok_; }
+  bool global_on() const override { return glob_; }
+  int set_global(bool on, std::string &err) override {
+    if (on && !glob_ok_) {
+      err = "the iteration through the global recursions is not available for this problem";
+      return DLMPC_EINVAL;
+    }
+    BENG_CHECK(hipStreamSynchronize(stream_));
+    glob_ = on;
+    BArgs &a = args_;
+    a.glob = on ? 1 : 0;
+    a.rb = on ? ny_ : 1;
+    a.rm = on ? 1 : int64_t(hs_->rs) * a.Bmax;
+    a.rl = on ? hs_->N : a.Bmax;
+    a.src_bs = a.rb;
+    a.src_rs = a.rl;
+    return DLMPC_OK;
   }
 
   int check(const double *x0_dev, std::string &err) override {
@@ -2291,6 +2435,160 @@ class BatchEngineT final : public BatchEngine {
       default: hipLaunchKernelGGL((bpsi_kernel<NX, 4, SPLIT>), dim3(n_units_), dim3(kPsiThreads), 0, stream_, x); break;
     }
   }
+  // Global recursions: availability and buffers. They need the row data and states of one time
+  // step and the input rows of one instance on chip, the input rows or the k-space coordinates of
+  // a patch for 16 instances on chip, and a plant that does not amplify (global_growth).
+  int init_global(std::string &err) {
+    const HostSetup &hs = *hs_;
+    BArgs &a = args_;
+    const int N = hs.N, NS = N * NX, nuT = hs.nu * (hs.T - 1);
+    glob_ok_ = false;
+    if (!split_ || nuT < 1 || NS > kSimStates) return DLMPC_OK;
+    sim_lds_ = (size_t(2) * kSimStates + size_t(N) * nuT) * sizeof(float);
+    sim_start_lds_ = (size_t(4) * kSimStates + size_t(N) * nuT) * sizeof(float);
+    int w32 = 32, k32 = 32;
+    for (int j = 0; j < N; ++j) {
+      w32 = std::max(w32, (int(hs.patch[j].size()) * nuT + 31) & ~31);
+      k32 = std::max(k32, (hs.kdim[j] + 31) & ~31);
+    }
+    // 32 instances per block where two blocks fit in a CU's LDS, else 16
+    const size_t per_inst = size_t(std::max(w32, k32) + 8) * 2 * sizeof(__bf16);
+    step_nt_ = (a.Bmax > 16 && 32 * per_inst <= kStepLds2) ? 2 : 1;
+    step_lds_ = size_t(16) * step_nt_ * per_inst;
+    if (sim_start_lds_ > kGlobLds || step_lds_ > kGlobLds || global_growth(hs) > kMaxGrowth) return DLMPC_OK;
+    a.sim_q = std::max(1, std::min(kSimParts, 256 / a.Bmax));  // parts of the row update: a CU each
+    step_mt_ = (k32 / 16 + kStepWaves - 1) / kStepWaves;
+    step_wn_ = (step_nt_ == 2 && k32 / 16 <= kStepWaves / 2) ? 2 : 1;
+    // state rows c N + m of A and of A'
+    std::vector<std::vector<std::pair<int32_t, float>>> row(NS), col(NS);
+    for (int m = 0; m < N; ++m)
+      for (int64_t q = hs.a_rowptr[m]; q < hs.a_rowptr[m + 1]; ++q)
+        for (int c = 0; c < NX; ++c)
+          for (int c2 = 0; c2 < NX; ++c2) {
+            const float v = float(hs.a_blocks[size_t(q) * NX * NX + c * NX + c2]);
+            if (v == 0.f) continue;
+            row[c * N + m].push_back({c2 * N + hs.a_colidx[q], v});
+            col[c2 * N + hs.a_colidx[q]].push_back({c * N + m, v});
+          }
+    int rc;
+    auto csr = [&](const std::vector<std::vector<std::pair<int32_t, float>>> &r, const int32_t **rp, const int32_t **ci,
+                   const float **va) {
+      std::vector<int32_t> p(1, 0), i;
+      std::vector<float> v;
+      for (const auto &x : r) {
+        for (const auto &e : x) {
+          i.push_back(e.first);
+          v.push_back(e.second);
+        }
+        p.push_back(int32_t(i.size()));
+      }
+      int q;
+      if ((q = up(p, rp, err)) || (q = up(i, ci, err))) return q;
+      return up(v, va, err);
+    };
+    if ((rc = csr(row, &a.prp, &a.pcol, &a.pval)) || (rc = csr(col, &a.trp, &a.tcol, &a.tval))) return rc;
+    std::vector<float> wt(ny_), lt(ny_), ut(ny_);
+    for (int m = 0; m < N; ++m)
+      for (int l = 0; l < hs.rs; ++l) {
+        wt[size_t(l) * N + m] = float(hs.w[size_t(m) * hs.rs + l]);
+        lt[size_t(l) * N + m] = float(hs.lb[size_t(m) * hs.rs + l]);
+        ut[size_t(l) * N + m] = float(hs.ub[size_t(m) * hs.rs + l]);
+      }
+    if ((rc = up(wt, &a.wT, err)) || (rc = up(lt, &a.lbT, err)) || (rc = up(ut, &a.ubT, err))) return rc;
+    std::vector<int64_t> uo(N + 1, 0), vo(N + 1, 0);
+    for (int j = 0; j < N; ++j) {
+      const int64_t mu = int64_t(hs.patch[j].size()) * nuT, k = hs.kdim[j];
+      uo[j + 1] = uo[j] + ((k + 15) / 16) * ((mu + 31) / 32) * 1024;
+      vo[j + 1] = vo[j] + ((mu + 15) / 16) * ((k + 31) / 32) * 1024;
+    }
+    std::vector<StepDesc> sd(N);
+    {
+      std::vector<int32_t> so(N);  // heaviest first
+      for (int j = 0; j < N; ++j) so[j] = j;
+      std::stable_sort(so.begin(), so.end(), [&](int x, int y) {
+        return hs.patch[x].size() * size_t(hs.kdim[x] + 64) > hs.patch[y].size() * size_t(hs.kdim[y] + 64);
+      });
+      int64_t ko = 0;
+      std::vector<int64_t> kof(N);
+      for (int j = 0; j < N; ko += (hs.kdim[j] + 31) & ~31, ++j) kof[j] = ko;
+      for (int q = 0; q < N; ++q) {
+        const int j = so[q];
+        sd[q] = {j, int32_t(hs.patch[j].size()), hs.kdim[j], 0, hs.tile_off[j], kof[j], uo[j], vo[j], hs.off_ptr[j]};
+      }
+    }
+    __bf16 *fu = nullptr, *fv = nullptr;
+    const size_t bm = size_t(a.Bmax);
+    if ((rc = up(uo, &a.ngu_off, err)) || (rc = up(sd, &a.sdesc, err)) || (rc = up(vo, &a.ngv_off, err)) || (rc = al(&fu, size_t(uo[N]), err)) ||
+        (rc = al(&fv, size_t(vo[N]), err)) || (rc = al(&a.bu, bm * N * nuT, err)) ||
+        (rc = al(&a.usum, bm * N * nuT, err)) || (rc = al(&a.gu, bm * N * nuT, err)) ||
+        (rc = al(&a.upart, size_t(hs.n_tiles) * nuT * a.Bw, err)) || (rc = al(&a.lam0, bm * NS, err)) ||
+        (rc = al(&a.rres, bm * 2 * N, err)) || (rc = al(&a.dlq, bm * kSimParts * N, err)))
+      return rc;
+    BENG_CHECK(hipMemset(fu, 0, sizeof(__bf16) * std::max<int64_t>(uo[N], 1)));
+    BENG_CHECK(hipMemset(fv, 0, sizeof(__bf16) * std::max<int64_t>(vo[N], 1)));
+    hipLaunchKernelGGL(bgfrag_kernel, dim3(N, 16), dim3(256), 0, nullptr, a.nb64, a.nb_off, a.kdim, a.tile_off, a.koff,
+                       a.ngu_off, a.ngv_off, hs.rs, NX * hs.T, fu, fv);
+    BENG_CHECK(hipGetLastError());
+    BENG_CHECK(hipDeviceSynchronize());
+    a.ngu = fu;
+    a.ngv = fv;
+    glob_ok_ = true;
+    return DLMPC_OK;
+  }
+  dim3 sim_threads() const { return dim3(std::min(kSimThreads, (hs_->N * NX + 63) & ~63)); }
+  int sim_rpt() const { return (hs_->N * NX + kSimThreads - 1) / kSimThreads; }
+  void launch_fwd(const BArgs &x) {
+    const dim3 g(args_.Bmax, args_.sim_q);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, g, sim_threads(), sim_lds_, stream_, x); };
+    switch (sim_rpt()) {
+      case 1: return go(bsim_fwd_kernel<NX, 1>);
+      case 2: return go(bsim_fwd_kernel<NX, 2>);
+      default: return go(bsim_fwd_kernel<NX, 4>);
+    }
+  }
+  void launch_adj(const BArgs &x) {
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(args_.Bmax), sim_threads(), sim_lds_, stream_, x); };
+    switch (sim_rpt()) {
+      case 1: return go(bsim_adj_kernel<NX, 1>);
+      case 2: return go(bsim_adj_kernel<NX, 2>);
+      default: return go(bsim_adj_kernel<NX, 4>);
+    }
+  }
+  void launch_sim_start(const int32_t *slots, int S, int pl) {
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(S), sim_threads(), sim_start_lds_, stream_, args_, slots, pl); };
+    switch (sim_rpt()) {
+      case 1: return go(bsim_start_kernel<NX, 1>);
+      case 2: return go(bsim_start_kernel<NX, 2>);
+      default: return go(bsim_start_kernel<NX, 4>);
+    }
+  }
+  void launch_step(const BArgs &x) {
+    const int nh = (args_.Bmax + 16 * step_nt_ - 1) / (16 * step_nt_);
+    const dim3 g((hs_->N + 7) / 8 * 8 * nh), t(kStepThreads);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, g, t, step_lds_, stream_, x); };
+    if (step_wn_ == 2) return go(bstep_kernel<NX, 1, 2, 2>);
+    if (step_nt_ == 2) {
+      switch (step_mt_) {
+        case 1: return go(bstep_kernel<NX, 1, 2, 1>);
+        case 2: return go(bstep_kernel<NX, 2, 2, 1>);
+        case 3: return go(bstep_kernel<NX, 3, 2, 1>);
+        default: return go(bstep_kernel<NX, 4, 2, 1>);
+      }
+    }
+    switch (step_mt_) {
+      case 1: return go(bstep_kernel<NX, 1, 1, 1>);
+      case 2: return go(bstep_kernel<NX, 2, 1, 1>);
+      case 3: return go(bstep_kernel<NX, 3, 1, 1>);
+      default: return go(bstep_kernel<NX, 4, 1, 1>);
+    }
+  }
+  void launch_gather(const BArgs &x) {
+    const size_t lds = size_t(args_.Bw) * ((hs_->nu * (hs_->T - 1)) | 1) * sizeof(float);
+    hipLaunchKernelGGL(bgather_kernel, dim3(hs_->N + args_.Bmax), dim3(256), lds, stream_, x);
+  }
+  bool glob_ok_ = false, glob_ = false;
+  int step_nt_ = 1, step_mt_ = 1, step_wn_ = 1;
+  size_t sim_lds_ = 0, sim_start_lds_ = 0, step_lds_ = 0;
   int nrt_ = 1, mtw_ = 1;
   int phi_ntw_ = 1;  // instance tiles per Phi-comp wave (autotuned)
   int psi_capx_ = kPsiCapDefault;  // Psi-comp split (autotuned)

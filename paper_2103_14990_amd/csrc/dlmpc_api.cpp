@@ -218,7 +218,8 @@ int setup_device(dlmpc_problem *p) {
 }
 
 // Autotuner cache (file named by DLMPC_TUNE_CACHE): one line per problem signature,
-// "<signature>|phi_ntw=<1|2> psi_capx=<n> sched=<0|1>".
+// "<signature>|phi_ntw=<1|2> psi_capx=<n> sched=<0|1|2> glob=<0|1>" (a line without glob names the
+// dense products).
 std::string tune_signature(const dlmpc_problem *p) {
   const HostSetup &h = p->hs;
   hipDeviceProp_t prop{};
@@ -231,7 +232,7 @@ std::string tune_signature(const dlmpc_problem *p) {
   return buf;
 }
 
-bool tune_cache_read(const std::string &sig, int *phi_ntw, int *psi_capx, int *sched) {
+bool tune_cache_read(const std::string &sig, int *phi_ntw, int *psi_capx, int *sched, int *glob) {
   const char *path = std::getenv("DLMPC_TUNE_CACHE");
   if (!path || !*path) return false;
   std::FILE *f = std::fopen(path, "r");
@@ -247,6 +248,8 @@ bool tune_cache_read(const std::string &sig, int *phi_ntw, int *psi_capx, int *s
       *phi_ntw = a;
       *psi_capx = b;
       *sched = c;
+      const size_t at = l.find(" glob=", bar);
+      *glob = at != std::string::npos && l[at + 6] == '1';
       found = true;
     }
   }
@@ -254,17 +257,19 @@ bool tune_cache_read(const std::string &sig, int *phi_ntw, int *psi_capx, int *s
   return found;
 }
 
-void tune_cache_write(const std::string &sig, int phi_ntw, int psi_capx, int sched) {
+void tune_cache_write(const std::string &sig, int phi_ntw, int psi_capx, int sched, int glob) {
   const char *path = std::getenv("DLMPC_TUNE_CACHE");
   if (!path || !*path) return;
   std::FILE *f = std::fopen(path, "a");
   if (!f) return;
-  std::fprintf(f, "%s|phi_ntw=%d psi_capx=%d sched=%d\n", sig.c_str(), phi_ntw, psi_capx, sched);
+  std::fprintf(f, "%s|phi_ntw=%d psi_capx=%d sched=%d glob=%d\n", sig.c_str(), phi_ntw, psi_capx, sched, glob);
   std::fclose(f);
 }
 
 // Times the batched-engine variants with max_batch instances from a zero-multiplier start (every
-// launch does the full work; x0 = 1 everywhere) and keeps the fastest Phi-comp and Psi-comp.
+// launch does the full work; x0 = 1 everywhere) and keeps the fastest Phi-comp and Psi-comp; then
+// the iteration through the global recursions, kept when its launches take less time than those
+// of the chosen dense variants.
 int tune_batch(dlmpc_problem *p) {
   const HostSetup &hs = p->hs;
   const int B = p->beng->bmax();
@@ -314,6 +319,19 @@ int tune_batch(dlmpc_problem *p) {
     for (int c = 0; c < 6; ++c)
       if (p->tune_psi_us[c] > 0.0 && p->tune_psi_us[c] < 0.99 * p->tune_psi_us[best_c]) best_c = c;
     if ((rc = p->beng->set_variant(ntw, caps[best_c], err))) return fail(rc, err);
+    if (!p->beng->global_available()) return DLMPC_OK;
+    double dense = p->tune_phi_us[ntw - 1] + p->tune_psi_us[best_c], t = 0.0, sum = 0.0;
+    if ((rc = time_k(2, &t))) return rc;
+    dense += t;
+    if ((rc = p->beng->set_global(true, err))) return fail(rc, err);
+    rc = p->beng->precompute(x, B, 1 << 20, -1.0, 1, nullptr, err);
+    if (!rc) rc = p->beng->start_alpha(z, err);
+    if (rc) return fail(rc, err);
+    for (int k = 0; k < 3; ++k) {
+      if ((rc = time_k(k, &t))) return rc;
+      sum += t;
+    }
+    if (sum > dense && (rc = p->beng->set_global(false, err))) return fail(rc, err);
     return DLMPC_OK;
   };
   const int rc = run();
@@ -352,11 +370,16 @@ int setup_batch(dlmpc_problem *p) {
   API_HIP(hipEventCreate(&p->ev_w1));
   // kernel variants: from the tuning cache, else timed here (before the graphs are captured:
   // they record the variant and the work-unit count), unless the caller fixed the defaults
-  if (!(p->opt.flags & DLMPC_FLAG_NO_TUNE)) {
-    int ntw = 0, capx = 0, sched = 0;
+  if (p->opt.flags & DLMPC_FLAG_NO_TUNE) {
+    // untimed: the global recursions wherever the problem allows them (faster from the 8 x 8 grid
+    // to the 1024-node mesh)
+    if (p->beng->global_available() && (rc = p->beng->set_global(true, err))) return fail(rc, err);
+  } else {
+    int ntw = 0, capx = 0, sched = 0, glob = 0;
     std::string err2;
-    if (tune_cache_read(tune_signature(p), &ntw, &capx, &sched) && !p->beng->set_variant(ntw, capx, err2)) {
+    if (tune_cache_read(tune_signature(p), &ntw, &capx, &sched, &glob) && !p->beng->set_variant(ntw, capx, err2)) {
       p->tune_cached = 1;
+      if (glob && p->beng->global_available() && (rc = p->beng->set_global(true, err))) return fail(rc, err);
     } else {
       rc = tune_batch(p);
       if (rc) return rc;
@@ -493,7 +516,7 @@ int choose_schedule(dlmpc_problem *p) {
     return DLMPC_OK;
   }
   const std::string sig = tune_signature(p);
-  int ntw = 0, capx = 0, sched = 0;
+  int ntw = 0, capx = 0, sched = 0, glob = 0;
   // candidates: 0 graph schedule with the dense Psi-comp, 1 persistent, 2 graph schedule with the
   // structured Psi-comp (cached as such; p->sched is 0 for it)
   auto apply = [&](int s) -> int {
@@ -502,7 +525,7 @@ int choose_schedule(dlmpc_problem *p) {
     p->eng->set_structured(s == 2);
     return capture_single(p);
   };
-  if (tune_cache_read(sig, &ntw, &capx, &sched) && (sched == 0 || (sched == 1 && can_persist) ||
+  if (tune_cache_read(sig, &ntw, &capx, &sched, &glob) && (sched == 0 || (sched == 1 && can_persist) ||
                                                     (sched == 2 && p->struct_ok))) {
     p->tune_cached = 1;
     return apply(sched);
@@ -531,7 +554,7 @@ int choose_schedule(dlmpc_problem *p) {
   ntw = 1;
   capx = 8;
   if (p->beng) p->beng->variant(&ntw, &capx, &nu);
-  tune_cache_write(sig, ntw, capx, best);
+  tune_cache_write(sig, ntw, capx, best, p->beng && p->beng->global_on() ? 1 : 0);
   return DLMPC_OK;
 }
 
@@ -778,6 +801,7 @@ int dlmpc_query(const dlmpc_problem *p, dlmpc_info *info) {
   info->batch_phi_ntw = 0;
   info->batch_psi_capx = 0;
   info->batch_psi_units = 0;
+  info->batch_global = p->beng && p->beng->global_on() ? 1 : 0;
   if (p->beng) p->beng->variant(&info->batch_phi_ntw, &info->batch_psi_capx, &info->batch_psi_units);
   for (int v = 0; v < 2; ++v) info->tune_phi_us[v] = p->tune_phi_us[v];
   for (int c = 0; c < 6; ++c) info->tune_psi_us[c] = p->tune_psi_us[c];

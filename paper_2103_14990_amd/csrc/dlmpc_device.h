@@ -36,7 +36,7 @@ struct Ctl {
   int32_t cg_k, pad3;  // CG steps of the streamed joins' trajectory start
   double rho;          // single-instance engine: the penalty of the current solve
   int32_t inner_iters;  // single-instance engine: nested-ADMM iterations of the solve (couplings)
-  int32_t pad4;
+  uint32_t n_stop;      // batched engine: stopped instances counted by the current decision pass
 };
 
 // Static work lists of the persistent schedule: block b runs Phi-comp for
@@ -179,6 +179,13 @@ struct BCtl {  // per-instance control block
   double eq_resid, box, u0dev, objective64;
 };
 
+// Column subsystem of a block of bstep_kernel: subsystem, patch size, null-space dimension, and the
+// offsets of its tiles, k-space vectors, fragments (ngu, ngv) and o_c.
+struct StepDesc {
+  int32_t j, p, k, pad;
+  int64_t tb, koff, uo, vo, offp;
+};
+
 struct BArgs {
   int32_t N, nx, nu, T, rs, Bmax;
   float rho;
@@ -258,6 +265,22 @@ struct BArgs {
   const int64_t *nb_off;
   double *y64;
   double *wchk;  // [Ktot][64] product operand of the check (W_j of each instance)
+  // Row vectors alpha and s: element (instance b, subsystem m, local row l) at b rb + m rm + l rl
+  // ([R][Bmax] for the dense products, [Bmax][rs][N] for the global recursions).
+  int64_t rb, rm, rl;
+  // Iteration through the global recursions (batch_global.h): input-row vectors [Bmax][N][nuT] (the
+  // rows of b, the sum U, g), the shares of U [tile][nuT][Bw], residual maxima [Bmax][2][N], lam_0
+  // [Bmax][nx][N], row data [rs][N], the state rows c N + m of A and of A' (CSR), and the input rows
+  // of the bases in fragment order.
+  int32_t glob, sim_q;  // sim_q: parts of an instance's row update
+  float *bu, *usum, *gu, *upart, *lam0;
+  double *rres, *dlq;  // dlq [Bmax][sim_q][N]: the parts' sums of (alpha - alpha_prev)^2
+  const float *wT, *lbT, *ubT;
+  const int32_t *prp, *pcol, *trp, *tcol;
+  const float *pval, *tval;
+  const int64_t *ngu_off, *ngv_off;
+  const __bf16 *ngu, *ngv;
+  const StepDesc *sdesc;  // [N], in dispatch order
   double *chkpart;  // [Bmax][parts][4] per-part maxima (eq, box, u0) and objective sums
 };
 
@@ -290,7 +313,14 @@ class BatchEngine {
   // mean; one of 2, 4, 8, 16, 1 << 20). Synchronises the engine's stream.
   virtual int set_variant(int phi_ntw, int psi_capx, std::string &err) = 0;
   virtual void variant(int *phi_ntw, int *psi_capx, int *n_units) const = 0;
-  // One kernel of an iteration: 0 bphi_kernel, 1 bpsi_kernel, 2 bdecide_kernel.
+  // Iteration through the plant's global recursions (split operands; batch_global.h): whether this
+  // problem allows it, and the switch between it and the dense products (before graph capture;
+  // the next solve must start with precompute). Synchronises the engine's stream.
+  virtual bool global_available() const = 0;
+  virtual int set_global(bool on, std::string &err) = 0;
+  virtual bool global_on() const = 0;
+  // One kernel of an iteration: 0 bphi_kernel, 1 bpsi_kernel, 2 bdecide_kernel (global recursions:
+  // 0 bsim_fwd_kernel, 1 bsim_adj_kernel and bstep_kernel, 2 bgather_kernel).
   virtual int launch_one(int k, std::string &err) = 0;
   virtual int output(double *u0_dev, std::string &err) = 0;
   // Base penalty of the solves started after this call (per-instance factors multiply it).
