@@ -228,8 +228,11 @@ typedef struct {
   int32_t factor_device; /* 1 if the column blocks were factored on the device, 0 on the host */
   int32_t factor_fallbacks; /* device factorisation: subsystems whose null basis came from the
                                Householder QR because Cholesky QR of S K met a tiny pivot */
-  /* Autotuner (dlmpc_setup). The single-instance schedule (graph or persistent, both timed over 32
-   * iterations) and the batched engine's kernel variants are chosen by timing at setup, or taken
+  /* Autotuner (dlmpc_setup). The single-instance schedule (graph or persistent, each timed over 32
+   * iterations in the standard form, all of Phi, Psi and Lambda in every iteration, and in the
+   * compact form of the cold start, row multipliers and null-space coordinates with Phi, Psi and
+   * Lambda written after the stop; the times reported are those of the faster form; given starts and
+   * couplings always run the standard form) and the batched engine's kernel variants are chosen by timing at setup, or taken
    * from the cache file named by the environment variable DLMPC_TUNE_CACHE (one line per problem
    * signature: sizes, precision, max_batch and the device's architecture; appended after a timed
    * setup). Batched variants: instance tiles per Phi-comp wave (1: each basis fragment feeds one
@@ -247,7 +250,9 @@ typedef struct {
                                structured Psi-comp (batch_psi_capx = 0; 0 us when not available) */
   /* Single-instance Psi-comp: 1 if the structured one (DLMPC_FLAG_STRUCTURED_PSI) runs, chosen
    * by the flag, or by timing at setup when no schedule flag is given (tune_structured_us: its
-   * per-iteration time on the graph schedule, 0 if not timed). */
+   * per-iteration time on the graph schedule, 0 if not timed). Its compact form multiplies with the
+   * input rows of the null bases between global recursions of the plant (plants of up to 4096
+   * states whose A^t grows by at most 32, in FP64 1000, over the horizon). */
   int32_t psi_structured;
   int32_t batch_global; /* 1 if the batched engine iterates through the global recursions of the plant (the
                            forward and adjoint recursions of A once per instance, products with the

@@ -910,6 +910,8 @@ __global__ __launch_bounds__(kConvBlock) void conv_kernel(KArgs<Tf> a, PsiUnits<
   }
 }
 
+#include "single_compact.h"
+
 // ------------------------------------------------------------------ persistent schedule
 
 // Grid-wide barrier of the persistent schedule (the grid is sized to be co-resident). Sense is
@@ -1739,6 +1741,65 @@ class EngineT final : public Engine {
 
   Ctl *ctl() override { return args_.ctl; }
 
+  int compact_modes(std::string &err) override {
+    if (cmodes_ < 0) {
+      const int rc = build_compact(err);
+      if (rc) return rc;
+    }
+    return cmodes_;
+  }
+
+  int compact_precompute(int mode, const double *x0_dev, int max_iter, double eps, double rho,
+                         std::string &err) override {
+    hipLaunchKernelGGL((cprep_kernel<Tf, NX>), dim3(hs_->N), dim3(kBlock), 0, stream_, args_, cargs(mode), x0_dev,
+                       max_iter, eps, rho);
+    ENG_CHECK(hipGetLastError());
+    return DLMPC_OK;
+  }
+
+  int compact_iteration(int mode, std::string &err) override {
+    const CArgs<Tf> &c = cargs(mode);
+    if (mode == kCompactGlobal) {
+      launch_csim(c, true);
+      ENG_CHECK(hipGetLastError());
+      launch_csim(c, false);
+    } else {
+      hipLaunchKernelGGL((crow_kernel<Tf, NX>), dim3(hs_->N + 1), dim3(kCRowThreads), 0, stream_, args_, c);
+    }
+    ENG_CHECK(hipGetLastError());
+    hipLaunchKernelGGL((cstep_kernel<Tf, NX>), dim3(c.n_units), dim3(kBlock), cstep_lds_[mode == kCompactGlobal],
+                       stream_, args_, c);
+    ENG_CHECK(hipGetLastError());
+    if (mode == kCompactGlobal) {
+      hipLaunchKernelGGL((crow_kernel<Tf, NX>), dim3(hs_->N), dim3(kCRowThreads), 0, stream_, args_, c);
+      ENG_CHECK(hipGetLastError());
+    }
+    return DLMPC_OK;
+  }
+
+  int compact_decide(int mode, std::string &err) override {
+    hipLaunchKernelGGL((cdecide_kernel<Tf, NX>), dim3(1), dim3(kCSimThreads), 0, stream_, args_, cargs(mode));
+    ENG_CHECK(hipGetLastError());
+    return DLMPC_OK;
+  }
+
+  int compact_solve(std::string &err) override {
+    // a group of lanes per row and per basis vector, where a workgroup has that many
+    const int need = std::max(hs_->N * hs_->rs * kCS1, int(std::max<int64_t>(hs_->sum_k, hs_->N)) * kCS2);
+    const int bd = std::min(kCSolveThreads, std::max(256, (need + 63) & ~63));
+    hipLaunchKernelGGL((csolve_kernel<Tf, NX>), dim3(1), dim3(bd), csolve_.total, stream_, args_, cd_, csolve_);
+    ENG_CHECK(hipGetLastError());
+    return DLMPC_OK;
+  }
+
+  int compact_finish(int mode, std::string &err) override {
+    const size_t lds = size_t(3) * std::max(hs_->k_max, 1) * sizeof(Tf);
+    const int gy = std::max(1, std::min(8, 1024 / std::max(hs_->N, 1)));
+    hipLaunchKernelGGL((cexpand_kernel<Tf, NX>), dim3(hs_->N, gy), dim3(kBlock), lds, stream_, args_, cargs(mode));
+    ENG_CHECK(hipGetLastError());
+    return DLMPC_OK;
+  }
+
   ~EngineT() override {
     for (void *p : owned_) (void)hipFree(p);
   }
@@ -1778,6 +1839,211 @@ class EngineT final : public Engine {
     *dst = const_cast<V *>(reinterpret_cast<const V *>(p));
     return DLMPC_OK;
   }
+
+  // Compact form: the dense variant's arguments cd_, the global one's cg_ (its own row order, bases
+  // and units; the k-space vectors, residuals and bases' offsets are shared).
+  const CArgs<Tf> &cargs(int mode) const { return mode == kCompactGlobal ? cg_ : cd_; }
+
+  void launch_csim(const CArgs<Tf> &c, bool fwd) {
+    const int NS = hs_->N * NX;
+    const dim3 g(fwd ? kCParts + 1 : 1);
+    auto pick = [&](auto ku) {
+      constexpr int KU = decltype(ku)::value;
+      auto go = [&](auto rpt, auto bd) {
+        constexpr int RPT = decltype(rpt)::value, BD = decltype(bd)::value;
+        const dim3 t(std::min(BD, (NS + 63) & ~63));
+        if (fwd)
+          hipLaunchKernelGGL((csim_fwd_kernel<Tf, NX, RPT, KU, BD>), g, t, 0, stream_, args_, c);
+        else
+          hipLaunchKernelGGL((csim_adj_kernel<Tf, NX, RPT, KU, BD>), g, t, 0, stream_, args_, c);
+      };
+      using I1 = std::integral_constant<int, 1>;
+      using I2 = std::integral_constant<int, 2>;
+      using I4 = std::integral_constant<int, 4>;
+      using B1 = std::integral_constant<int, 1024>;
+      if (NS <= 1024) return go(I1{}, B1{});
+      if (NS <= 2048) return go(I2{}, B1{});
+      go(I4{}, B1{});
+    };
+    if (hs_->nu == 1)  // inputs kept in registers: the first one or two of every subsystem
+      pick(std::integral_constant<int, 1>{});
+    else
+      pick(std::integral_constant<int, 2>{});
+  }
+
+  int build_compact(std::string &err) {
+    const HostSetup &hs = *hs_;
+    const int N = hs.N, NS = N * NX, nuT = hs.nu * (hs.T - 1), rs = hs.rs;
+    const int64_t R = int64_t(N) * rs, K = hs.sum_k;
+    int rc, modes = 0;
+    // 32-bit offsets: of the tiles' rows in the bases, and in the shares
+    if (hs.nb_off[N] >= (int64_t(1) << 32)) {
+      cmodes_ = 0;
+      return DLMPC_OK;
+    }
+    CArgs<Tf> c{};
+    std::vector<int64_t> koff(N + 1, 0);
+    for (int j = 0; j < N; ++j) koff[j + 1] = koff[j] + hs.kdim[j];
+    std::vector<double> on2(size_t(N) * NX, 0.0);
+    for (int j = 0; j < N; ++j) {
+      const int D = int(hs.patch[j].size()) * rs, ld = padded_ld(D);
+      for (int q = 0; q < NX; ++q)
+        for (int r = 0; r < D; ++r) {
+          const double o = hs.off[hs.off_ptr[j] + size_t(q) * ld + r];
+          on2[size_t(j) * NX + q] += o * o;
+        }
+    }
+    if ((rc = upload(koff, &c.koff, err)) || (rc = upload(on2, &c.on2, err)) ||
+        (rc = upload(hs.tile_rsub, &c.rsub, err)) || (rc = alloc(&c.al, size_t(3 * R), err)) ||
+        (rc = alloc(&c.s, size_t(2 * R), err)) || (rc = alloc(&c.bv, size_t(R), err)) ||
+        (rc = alloc(&c.tau, size_t(K), err)) || (rc = alloc(&c.eta, size_t(K), err)) ||
+        (rc = alloc(&c.v, size_t(2 * K), err)) || (rc = alloc(&c.xn, size_t(N), err)) ||
+        (rc = alloc(&c.dlq, size_t(N) * (1 + kCParts), err)) || (rc = alloc(&c.sdl, size_t(N), err)) ||
+        (rc = alloc(&c.od, size_t(N) * NX, err)))
+      return rc;
+    // units of basis vectors (those of one subsystem consecutive) and row-side tiles
+    auto lists = [&](CArgs<Tf> &x, int rows, const std::vector<int64_t> &boff) {
+      std::vector<CUnit> unit;
+      std::vector<int32_t> ufirst(N + 1, 0);
+      std::vector<CTile> ct(size_t(hs.n_tiles));
+      for (int64_t q = 0; q < hs.n_tiles; ++q) {
+        const int j = hs.rt_col[q];
+        ct[q] = {uint32_t(boff[j] + (hs.rt_tile[q] - hs.tile_off[j]) * rows),
+                 padded_ld(int(hs.patch[j].size()) * rows), hs.kdim[j], int32_t(koff[j]), j, 0};
+      }
+      int64_t so = 0;
+      for (int j = 0; j < N; ++j) {
+        ufirst[j] = int32_t(unit.size());
+        for (int i0 = 0; i0 < std::max(hs.kdim[j], 1); i0 += kP1Cols) {
+          unit.push_back({j, i0, int32_t(hs.patch[j].size()), hs.kdim[j], hs.tile_off[j], boff[j], koff[j], so});
+          so += padded_ld(int(hs.patch[j].size()) * rows);
+        }
+      }
+      ufirst[N] = int32_t(unit.size());
+      std::vector<int32_t> sptr(N + 1, 0);
+      std::vector<uint32_t> soff;
+      for (int m = 0; m < N; ++m) {
+        for (int64_t q = hs.rt_ptr[m]; q < hs.rt_ptr[m + 1]; ++q) {
+          const int j = hs.rt_col[q];
+          for (int u = ufirst[j]; u < ufirst[j + 1]; ++u)
+            soff.push_back(uint32_t(unit[u].so + (hs.rt_tile[q] - hs.tile_off[j]) * rows));
+        }
+        sptr[m + 1] = int32_t(soff.size());
+      }
+      x.rows = rows;
+      x.n_units = ufirst[N];
+      int q;
+      if ((q = upload(unit, &x.unit, err)) || (q = upload(ufirst, &x.ufirst, err)) || (q = upload(ct, &x.ct, err)) ||
+          (q = upload(boff, &x.boff, err)) ||
+          (q = upload(sptr, &x.sptr, err)) || (q = upload(soff, &x.soff, err)) ||
+          (q = alloc(&x.share, size_t(so), err)) || (q = alloc(&x.part, size_t(2) * ufirst[N], err)))
+        return q;
+      return 0;
+    };
+    cd_ = c;
+    cd_.basis = args_.nb;
+    if ((rc = lists(cd_, rs, hs.nb_off))) return rc;
+    cstep_lds_[0] = size_t(padded_ld(hs.d_col_max)) * sizeof(Tf);
+    if (cstep_lds_[0] <= kCStepLds) modes |= 1 << kCompactDense;
+    // one workgroup: everything in LDS
+    {
+      uint32_t at = 0;
+      auto put = [&](size_t n, size_t sz) {
+        at = uint32_t((at + 15) & ~15u);
+        const uint32_t o = at;
+        at += uint32_t(std::min<size_t>(n * sz, size_t(1) << 24));
+        return o;
+      };
+      CSolveLds o{};
+      const size_t r = size_t(R), k = size_t(K), n = size_t(N);
+      o.basis = put(size_t(hs.nb_off[N]), sizeof(Tf));
+      for (uint32_t *x : {&o.al, &o.ap, &o.s, &o.bv, &o.w, &o.lb, &o.ub}) *x = put(r, sizeof(Tf));
+      o.d = put(r, 8);
+      o.tau = put(k, sizeof(Tf));
+      o.eta = put(k, sizeof(Tf));
+      o.v = put(2 * k, sizeof(Tf));
+      o.cw = put(k, sizeof(Tf));
+      o.e2 = put(k, 8);
+      o.d2 = put(k, 8);
+      size_t terms = 0, sup = 0;
+      for (int64_t q = 0; q < hs.n_tiles; ++q) terms += size_t(hs.kdim[hs.rt_col[q]]);
+      for (int j = 0; j < N; ++j) sup += hs.patch[j].size() * size_t(rs);
+      o.rt = put(n + 1, 4);
+      o.tm = put(terms, 8);
+      o.sp = put(n + 1, 4);
+      o.sr = put(sup, 4);
+      o.vj = put(k, 16);
+      o.cj = put(n, 8);
+      o.nr = put(n, sizeof(Tf));
+      o.total = at;
+      if (at <= kCSolveLds) {
+        csolve_ = o;
+        modes |= 1 << kCompactBlock;
+      }
+    }
+    // global recursions: states of one step on chip, and a plant that does not amplify (FP64
+    // has the digits to spare: its limit is the growth that costs six of them)
+    const double gmax = sizeof(Tf) == 8 ? 1e3 : 32.0;
+    if (nuT >= 1 && NS <= kCMaxStates && struct_ready_ && plant_growth(hs) <= gmax) {
+      CArgs<Tf> g = c;
+      g.glob = 1;
+      std::vector<std::vector<std::pair<int32_t, Tf>>> row(NS), col(NS);
+      for (int m = 0; m < N; ++m)
+        for (int64_t q = hs.a_rowptr[m]; q < hs.a_rowptr[m + 1]; ++q)
+          for (int e = 0; e < NX; ++e)
+            for (int f = 0; f < NX; ++f) {
+              const Tf v = static_cast<Tf>(hs.a_blocks[size_t(q) * NX * NX + e * NX + f]);
+              if (v == Tf(0)) continue;
+              row[e * N + m].push_back({f * N + hs.a_colidx[q], v});
+              col[f * N + hs.a_colidx[q]].push_back({e * N + m, v});
+            }
+      auto csr = [&](const std::vector<std::vector<std::pair<int32_t, Tf>>> &r, const int32_t **rp,
+                     const int32_t **ci, const Tf **va) {
+        std::vector<int32_t> p(1, 0), i;
+        std::vector<Tf> v;
+        for (const auto &x : r) {
+          for (const auto &e : x) {
+            i.push_back(e.first);
+            v.push_back(e.second);
+          }
+          p.push_back(int32_t(i.size()));
+        }
+        int q;
+        if ((q = upload(p, rp, err)) || (q = upload(i, ci, err))) return q;
+        return upload(v, va, err);
+      };
+      std::vector<Tf> wt(R), lt(R), ut(R);
+      for (int m = 0; m < N; ++m)
+        for (int l = 0; l < rs; ++l) {
+          wt[size_t(l) * N + m] = static_cast<Tf>(hs.w[size_t(m) * rs + l]);
+          lt[size_t(l) * N + m] = static_cast<Tf>(hs.lb[size_t(m) * rs + l]);
+          ut[size_t(l) * N + m] = static_cast<Tf>(hs.ub[size_t(m) * rs + l]);
+        }
+      std::vector<int64_t> boff(N + 1, 0);
+      for (int j = 0; j < N; ++j)
+        boff[j + 1] = boff[j] + int64_t((int(hs.patch[j].size()) * nuT + 3) & ~3) * hs.kdim[j];
+      if ((rc = csr(row, &g.prp, &g.pcol, &g.pval)) || (rc = csr(col, &g.trp, &g.tcol, &g.tval)) ||
+          (rc = upload(wt, &g.w, err)) || (rc = upload(lt, &g.lb, err)) || (rc = upload(ut, &g.ub, err)) ||
+          (rc = alloc(&g.us, size_t(N) * nuT, err)) || (rc = alloc(&g.g, size_t(N) * nuT, err)) ||
+          (rc = alloc(&g.lam0, size_t(NS), err)) || (rc = lists(g, nuT, boff)))
+        return rc;
+      g.bblk = sa_.bblk;
+      g.basis = sa_.nbu;  // the structured Psi-comp's input rows, in the same layout
+      cg_ = g;
+      int pm = 1;
+      for (int j = 0; j < N; ++j) pm = std::max(pm, int(hs.patch[j].size()));
+      cstep_lds_[1] = size_t((pm * nuT + 3) & ~3) * sizeof(Tf);
+      if (cstep_lds_[1] <= kCStepLds) modes |= 1 << kCompactGlobal;
+    }
+    cmodes_ = modes;
+    return DLMPC_OK;
+  }
+  static constexpr size_t kCSolveLds = 150 * 1024;
+  static constexpr size_t kCStepLds = 44 * 1024;  // one patch's rows, beside the shares' 16 KB
+  int cmodes_ = -1;
+  CArgs<Tf> cd_{}, cg_{};
+  CSolveLds csolve_{};
+  size_t cstep_lds_[2] = {0, 0};
 
   const HostSetup *hs_ = nullptr;
   hipStream_t stream_ = nullptr;

@@ -21,7 +21,7 @@
 // The recursions run in FP32; products accumulate over fewer rows, so the iterate is closer to
 // the FP64 one than through the dense bases (u(0) after 50 iterations on the 16 x 16 boxed grid:
 // 6e-7 against 2e-6 relative). A plant whose A^t grows over the horizon amplifies the rounding of
-// U in x; such plants keep the dense products (see global_growth in batch_kernels.hip).
+// U in x; such plants keep the dense products (see kMaxGrowth in batch_kernels.hip).
 #pragma once
 
 constexpr int kSimThreads = 1024;
@@ -45,7 +45,7 @@ __device__ __forceinline__ void lds_barrier() {
 // that the loop over the entries has no lane masks; states are two LDS buffers kSimStates apart.
 template <int RPT>
 struct RowEll {
-  int e0[RPT], n[RPT], nw[RPT], idx[RPT][kSimNE];
+  int e0[RPT], n[RPT], nw[RPT], idx[RPT][kSimNE];  // idx: byte offsets of the states
   float val[RPT][kSimNE];
   __device__ __forceinline__ void load(const int32_t *rp, const int32_t *col, const float *v, int NS) {
 #pragma unroll
@@ -59,7 +59,7 @@ struct RowEll {
       nw[i] = __builtin_amdgcn_readfirstlane(w);
 #pragma unroll
       for (int e = 0; e < kSimNE; ++e) {
-        idx[i][e] = e < n[i] ? col[e0[i] + e] : 0;
+        idx[i][e] = e < n[i] ? col[e0[i] + e] * int(sizeof(float)) : 0;
         val[i][e] = e < n[i] ? v[e0[i] + e] : 0.f;
       }
     }
@@ -69,7 +69,7 @@ struct RowEll {
 #pragma unroll
     for (int e = 0; e < kSimNE; ++e) {
       if (e >= nw[i]) break;
-      s += val[i][e] * x[idx[i][e]];
+      s += val[i][e] * *reinterpret_cast<const float *>(reinterpret_cast<const char *>(x) + idx[i][e]);
     }
     for (int e = kSimNE; e < n[i]; ++e) s += v[e0[i] + e] * x[col[e0[i] + e]];
     return s;
@@ -267,22 +267,30 @@ __global__ __launch_bounds__(kSimThreads) void bsim_adj_kernel(BArgs a) {
   const int64_t R = int64_t(N) * a.rs, plane = int64_t(a.Bmax) * R;
   const bool warm = a.ctl->warm != 0;
   const int it = a.ctl->iters + 1, cur = it & 1;
-  if (!initp && ph < 0)
+  auto sum_parts = [&]() {
+    if (initp || ph >= 0) return;
     for (int m = tid; m < N; m += bd) {
-      double d = 0.0;
-      for (int q = 0; q < a.sim_q; ++q) d += a.dlq[(int64_t(b) * a.sim_q + q) * N + m];
+      double x[kSimParts], d = 0.0;  // all parts in flight
+#pragma unroll
+      for (int q = 0; q < kSimParts; ++q) x[q] = a.dlq[(int64_t(b) * a.sim_q + min(q, a.sim_q - 1)) * N + m];
+#pragma unroll
+      for (int q = 0; q < kSimParts; ++q) d += q < a.sim_q ? x[q] : 0.0;
       a.dlm[int64_t(b) * N + m] = d;
     }
-  if (!warm && it == 1 && !initp) return;  // alpha^1 = 0
+  };
+  if (!warm && it == 1 && !initp) return sum_parts();  // alpha^1 = 0
   const float *src = initp ? a.src + int64_t(b) * a.src_bs
                      : (ph < 0 || ph > cg_k) ? a.alpha + cur * plane + b * R
                      : ph < cg_k ? a.cg_p + b * R : a.cg_x + b * R;
   float *xa = sim_lds, *xb = xa + kSimStates, *uv = xb + kSimStates;
+  int rr[RPT];  // this thread's state rows (clamped)
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) rr[i] = min(tid + i * bd, NS - 1);
   constexpr int kAhead = 4;
   float v[kAhead][RPT];
   auto fetch = [&](int t, float *f) {
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) f[i] = t >= 0 ? src[t * NS + min(tid + i * bd, NS - 1)] : 0.f;
+    for (int i = 0; i < RPT; ++i) f[i] = t >= 0 ? src[t * NS + rr[i]] : 0.f;
   };
 #pragma unroll
   for (int q = 0; q < kAhead; ++q) fetch(T - 1 - q, v[q]);
@@ -349,6 +357,7 @@ __global__ __launch_bounds__(kSimThreads) void bsim_adj_kernel(BArgs a) {
     if (t - 2 >= tl) step(t - 2, xb, xa, v[2]);
     if (t - 3 >= tl) step(t - 3, xa, xb, v[3]);
   }
+  sum_parts();
   lds_barrier();
   for (int e = tid; e < NU; e += bd) a.gu[int64_t(b) * NU + e] = uv[e];
 }

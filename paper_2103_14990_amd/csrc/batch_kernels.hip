@@ -1613,40 +1613,14 @@ __global__ void bfragu_kernel(const double *__restrict__ nb, const int64_t *__re
 constexpr int kPsiCaps[] = {2, 4, 8, 16, 1 << 20};
 constexpr int kPsiCapDefault = 8;
 
-// Growth of the plant over the horizon: largest |A^t v|_inf / |v|_inf over t < T and eight fixed sign
-// vectors v (the sum of squares of a row of A^t shows in every one of them). The limit lies where the
-// recursions' rounding begins to cost more than the dense products': relative error of u(0) after 40
+// Largest growth of A^t over the horizon (plant_growth) for the global recursions. The limit lies where
+// their rounding begins to cost more than the dense products': relative error of u(0) after 40
 // iterations against FP64, recursions / dense, emulated on random plants: growth 9 1.2e-6 / 2.6e-6, 46
 // 4.4e-6 / 2.8e-6, 93 3.4e-6 / 3.8e-6, 670 4.0e-6 / 1.9e-6, 2700 7.6e-6 / 2.0e-6; the swing networks
 // and the paper's chain, 2 to 15, have 5e-7 / 2e-6.
 constexpr double kMaxGrowth = 32.0;
 constexpr size_t kGlobLds = 150 * 1024;  // on-chip staging of one block (160 KB per CU)
 constexpr size_t kStepLds2 = 71 * 1024;  // two blocks per CU, beside their 9 KB of static LDS
-double global_growth(const HostSetup &hs) {
-  const int N = hs.N, nx = hs.nx;
-  double g = 0.0;
-  for (int v = 0; v < 8; ++v) {
-    std::vector<double> x(size_t(N) * nx), y(size_t(N) * nx);
-    uint64_t h = 0x9e3779b97f4a7c15ull * uint64_t(v + 1);
-    for (auto &e : x) {
-      h = h * 6364136223846793005ull + 1442695040888963407ull;
-      e = (h >> 63) ? 1.0 : -1.0;
-    }
-    for (int t = 1; t < hs.T; ++t) {
-      for (int m = 0; m < N; ++m)
-        for (int c = 0; c < nx; ++c) {
-          double s = 0.0;
-          for (int64_t q = hs.a_rowptr[m]; q < hs.a_rowptr[m + 1]; ++q)
-            for (int c2 = 0; c2 < nx; ++c2)
-              s += hs.a_blocks[size_t(q) * nx * nx + c * nx + c2] * x[size_t(hs.a_colidx[q]) * nx + c2];
-          y[size_t(m) * nx + c] = s;
-          g = std::max(g, std::fabs(s));
-        }
-      x.swap(y);
-    }
-  }
-  return g;
-}
 
 struct PsiSplit {
   std::vector<int32_t> pu_j, pu_r0, pu_r1, pu_p, pj_n, pj_first;
@@ -2437,7 +2411,7 @@ class BatchEngineT final : public BatchEngine {
   }
   // Global recursions: availability and buffers. They need the row data and states of one time
   // step and the input rows of one instance on chip, the input rows or the k-space coordinates of
-  // a patch for 16 instances on chip, and a plant that does not amplify (global_growth).
+  // a patch for 16 instances on chip, and a plant that does not amplify (plant_growth).
   int init_global(std::string &err) {
     const HostSetup &hs = *hs_;
     BArgs &a = args_;
@@ -2455,7 +2429,7 @@ class BatchEngineT final : public BatchEngine {
     const size_t per_inst = size_t(std::max(w32, k32) + 8) * 2 * sizeof(__bf16);
     step_nt_ = (a.Bmax > 16 && 32 * per_inst <= kStepLds2) ? 2 : 1;
     step_lds_ = size_t(16) * step_nt_ * per_inst;
-    if (sim_start_lds_ > kGlobLds || step_lds_ > kGlobLds || global_growth(hs) > kMaxGrowth) return DLMPC_OK;
+    if (sim_start_lds_ > kGlobLds || step_lds_ > kGlobLds || plant_growth(hs) > kMaxGrowth) return DLMPC_OK;
     a.sim_q = std::max(1, std::min(kSimParts, 256 / a.Bmax));  // parts of the row update: a CU each
     step_mt_ = (k32 / 16 + kStepWaves - 1) / kStepWaves;
     step_wn_ = (step_nt_ == 2 && k32 / 16 <= kStepWaves / 2) ? 2 : 1;

@@ -30,6 +30,11 @@ struct dlmpc_problem {
   hipGraphExec_t gexec[kGraphs] = {};
   int K = 32;  // fixed chunk when check_every > 0; otherwise the first chunk
   int sched = 0;  // 0 = graph, 1 = persistent
+  // compact form of cold-started single solves (0: not used; chosen by timing at setup), with
+  // graphs of its own; couplings and given starts run the standard form on `sched`
+  int compact = 0;
+  hipGraph_t cgraph[kGraphs] = {};
+  hipGraphExec_t cgexec[kGraphs] = {};
   double tune_graph_us = 0.0, tune_persistent_us = 0.0;
   // batched-engine autotuning: per-launch us of the Phi-comp variants (1, 2 instance tiles per
   // wave) and of the Psi-comp splits (kPsiCaps order); 1 if the choice came from the cache
@@ -100,6 +105,10 @@ void release_device(dlmpc_problem *p) {
     p->sgraph[g] = nullptr;
     p->gexec[g] = nullptr;
     p->graph[g] = nullptr;
+    if (p->cgexec[g]) (void)hipGraphExecDestroy(p->cgexec[g]);
+    if (p->cgraph[g]) (void)hipGraphDestroy(p->cgraph[g]);
+    p->cgexec[g] = nullptr;
+    p->cgraph[g] = nullptr;
     p->bgexec[g] = nullptr;
     p->bgraph[g] = nullptr;
   }
@@ -163,6 +172,33 @@ int capture_single(dlmpc_problem *p) {
   API_HIP(hipStreamSynchronize(p->stream));
   return DLMPC_OK;
 }
+
+// (Re)captures the compact iteration's graphs of 2^g iterations (g >= first), each closed by its
+// decision.
+int capture_compact(dlmpc_problem *p, int mode, int first = 0) {
+  std::string err;
+  API_HIP(hipStreamSynchronize(p->stream));
+  for (int g = first; g < dlmpc_problem::kGraphs; ++g) {
+    if (p->cgexec[g]) (void)hipGraphExecDestroy(p->cgexec[g]);
+    if (p->cgraph[g]) (void)hipGraphDestroy(p->cgraph[g]);
+    p->cgexec[g] = nullptr;
+    p->cgraph[g] = nullptr;
+    API_HIP(hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
+    int rc = DLMPC_OK;
+    for (int i = 0; i < (1 << g) && !rc; ++i) rc = p->eng->compact_iteration(mode, err);
+    if (!rc) rc = p->eng->compact_decide(mode, err);
+    if (rc) {
+      hipGraph_t gr = nullptr;
+      (void)hipStreamEndCapture(p->stream, &gr);
+      if (gr) (void)hipGraphDestroy(gr);
+      return fail(rc, err);
+    }
+    API_HIP(hipStreamEndCapture(p->stream, &p->cgraph[g]));
+    API_HIP(hipGraphInstantiate(&p->cgexec[g], p->cgraph[g], nullptr, nullptr, 0));
+  }
+  API_HIP(hipStreamSynchronize(p->stream));
+  return DLMPC_OK;
+}
 int setup_batch(dlmpc_problem *p);
 
 int setup_device(dlmpc_problem *p) {
@@ -218,8 +254,8 @@ int setup_device(dlmpc_problem *p) {
 }
 
 // Autotuner cache (file named by DLMPC_TUNE_CACHE): one line per problem signature,
-// "<signature>|phi_ntw=<1|2> psi_capx=<n> sched=<0|1|2> glob=<0|1>" (a line without glob names the
-// dense products).
+// "<signature>|phi_ntw=<1|2> psi_capx=<n> sched=<0|1|2> glob=<0|1> comp=<0..3>" (a line without glob
+// names the dense products, one without comp the standard form of single solves).
 std::string tune_signature(const dlmpc_problem *p) {
   const HostSetup &h = p->hs;
   hipDeviceProp_t prop{};
@@ -232,7 +268,7 @@ std::string tune_signature(const dlmpc_problem *p) {
   return buf;
 }
 
-bool tune_cache_read(const std::string &sig, int *phi_ntw, int *psi_capx, int *sched, int *glob) {
+bool tune_cache_read(const std::string &sig, int *phi_ntw, int *psi_capx, int *sched, int *glob, int *comp) {
   const char *path = std::getenv("DLMPC_TUNE_CACHE");
   if (!path || !*path) return false;
   std::FILE *f = std::fopen(path, "r");
@@ -250,6 +286,8 @@ bool tune_cache_read(const std::string &sig, int *phi_ntw, int *psi_capx, int *s
       *sched = c;
       const size_t at = l.find(" glob=", bar);
       *glob = at != std::string::npos && l[at + 6] == '1';
+      const size_t ac = l.find(" comp=", bar);
+      *comp = ac != std::string::npos && l[ac + 6] >= '0' && l[ac + 6] <= '3' ? l[ac + 6] - '0' : 0;
       found = true;
     }
   }
@@ -257,12 +295,13 @@ bool tune_cache_read(const std::string &sig, int *phi_ntw, int *psi_capx, int *s
   return found;
 }
 
-void tune_cache_write(const std::string &sig, int phi_ntw, int psi_capx, int sched, int glob) {
+void tune_cache_write(const std::string &sig, int phi_ntw, int psi_capx, int sched, int glob, int comp) {
   const char *path = std::getenv("DLMPC_TUNE_CACHE");
   if (!path || !*path) return;
   std::FILE *f = std::fopen(path, "a");
   if (!f) return;
-  std::fprintf(f, "%s|phi_ntw=%d psi_capx=%d sched=%d glob=%d\n", sig.c_str(), phi_ntw, psi_capx, sched, glob);
+  std::fprintf(f, "%s|phi_ntw=%d psi_capx=%d sched=%d glob=%d comp=%d\n", sig.c_str(), phi_ntw, psi_capx, sched, glob,
+               comp);
   std::fclose(f);
 }
 
@@ -375,9 +414,9 @@ int setup_batch(dlmpc_problem *p) {
     // to the 1024-node mesh)
     if (p->beng->global_available() && (rc = p->beng->set_global(true, err))) return fail(rc, err);
   } else {
-    int ntw = 0, capx = 0, sched = 0, glob = 0;
+    int ntw = 0, capx = 0, sched = 0, glob = 0, comp = 0;
     std::string err2;
-    if (tune_cache_read(tune_signature(p), &ntw, &capx, &sched, &glob) && !p->beng->set_variant(ntw, capx, err2)) {
+    if (tune_cache_read(tune_signature(p), &ntw, &capx, &sched, &glob, &comp) && !p->beng->set_variant(ntw, capx, err2)) {
       p->tune_cached = 1;
       if (glob && p->beng->global_available() && (rc = p->beng->set_global(true, err))) return fail(rc, err);
     } else {
@@ -483,6 +522,35 @@ int time_schedule(dlmpc_problem *p, int sched, int n, double *us_per_iter) {
   return DLMPC_OK;
 }
 
+// The same for the compact form.
+int time_compact(dlmpc_problem *p, int mode, int n, double *us_per_iter) {
+  std::string err;
+  const HostSetup &hs = p->hs;
+  std::vector<double> ones(size_t(hs.N) * hs.nx, 1.0);
+  API_HIP(hipMemcpy(p->d_x0, ones.data(), ones.size() * sizeof(double), hipMemcpyHostToDevice));
+  int g = 0;  // n is a power of two that has a graph
+  while ((2 << g) <= n && g + 1 < dlmpc_problem::kGraphs) ++g;
+  int rc = mode == dlmpc::kCompactBlock ? DLMPC_OK : capture_compact(p, mode, g);
+  if (rc) return rc;
+  float best = 1e30f;
+  for (int rep = 0; rep < 2; ++rep) {
+    if ((rc = p->eng->compact_precompute(mode, p->d_x0, n, -1.0, p->opt.rho, err))) return fail(rc, err);
+    API_HIP(hipEventRecord(p->ev_t0, p->stream));
+    if (mode == dlmpc::kCompactBlock) {
+      if ((rc = p->eng->compact_solve(err))) return fail(rc, err);
+    } else if ((rc = launch_graphs(p->cgexec, p->stream, n))) {
+      return rc;
+    }
+    API_HIP(hipEventRecord(p->ev_t1, p->stream));
+    API_HIP(hipStreamSynchronize(p->stream));
+    float ms = 0.f;
+    API_HIP(hipEventElapsedTime(&ms, p->ev_t0, p->ev_t1));
+    best = std::min(best, ms);
+  }
+  *us_per_iter = 1e3 * double(best) / n;
+  return DLMPC_OK;
+}
+
 int choose_schedule(dlmpc_problem *p) {
   const uint32_t f = p->opt.flags;
   const bool can_persist = p->eng->persistent_grid() > 0;
@@ -516,7 +584,8 @@ int choose_schedule(dlmpc_problem *p) {
     return DLMPC_OK;
   }
   const std::string sig = tune_signature(p);
-  int ntw = 0, capx = 0, sched = 0, glob = 0;
+  int rc = DLMPC_OK;
+  int ntw = 0, capx = 0, sched = 0, glob = 0, comp = 0;
   // candidates: 0 graph schedule with the dense Psi-comp, 1 persistent, 2 graph schedule with the
   // structured Psi-comp (cached as such; p->sched is 0 for it)
   auto apply = [&](int s) -> int {
@@ -525,14 +594,18 @@ int choose_schedule(dlmpc_problem *p) {
     p->eng->set_structured(s == 2);
     return capture_single(p);
   };
-  if (tune_cache_read(sig, &ntw, &capx, &sched, &glob) && (sched == 0 || (sched == 1 && can_persist) ||
+  std::string err;
+  const int modes = p->eng->compact_modes(err);
+  if (modes < 0) return fail(modes, err);
+  if (tune_cache_read(sig, &ntw, &capx, &sched, &glob, &comp) && (comp == 0 || (modes >> comp & 1)) && (sched == 0 || (sched == 1 && can_persist) ||
                                                     (sched == 2 && p->struct_ok))) {
     p->tune_cached = 1;
+    p->compact = comp;
+    if ((comp == dlmpc::kCompactDense || comp == dlmpc::kCompactGlobal) && (rc = capture_compact(p, comp))) return rc;
     return apply(sched);
   }
   const int n = 32;
-  int rc = time_schedule(p, 0, n, &p->tune_graph_us);
-  if (rc) return rc;
+  if ((rc = time_schedule(p, 0, n, &p->tune_graph_us))) return rc;
   if (can_persist) {
     rc = time_schedule(p, 1, n, &p->tune_persistent_us);
     if (rc) return rc;
@@ -548,13 +621,32 @@ int choose_schedule(dlmpc_problem *p) {
     best = 1;
     best_us = p->tune_persistent_us;
   }
-  if (p->struct_ok && p->tune_structured_us < best_us) best = 2;
+  if (p->struct_ok && p->tune_structured_us < best_us) {
+    best = 2;
+    best_us = p->tune_structured_us;
+  }
   if ((rc = apply(best))) return rc;
+  // the compact form beside each of the three: whole bases, input rows, one launch; the
+  // tuning times report the faster form of each
+  double *tune[4] = {nullptr, &p->tune_graph_us, &p->tune_structured_us, &p->tune_persistent_us};
+  for (int m : {dlmpc::kCompactDense, dlmpc::kCompactGlobal, dlmpc::kCompactBlock}) {
+    if (!(modes >> m & 1)) continue;
+    double t = 0.0;
+    if ((rc = time_compact(p, m, n, &t))) return rc;
+    if (*tune[m] <= 0.0 || t < *tune[m]) *tune[m] = t;
+    if (t < best_us) {
+      best_us = t;
+      p->compact = m;
+    }
+  }
+  if ((p->compact == dlmpc::kCompactDense || p->compact == dlmpc::kCompactGlobal) &&
+      (rc = capture_compact(p, p->compact)))
+    return rc;
   int nu = 0;
   ntw = 1;
   capx = 8;
   if (p->beng) p->beng->variant(&ntw, &capx, &nu);
-  tune_cache_write(sig, ntw, capx, best, p->beng && p->beng->global_on() ? 1 : 0);
+  tune_cache_write(sig, ntw, capx, best, p->beng && p->beng->global_on() ? 1 : 0, p->compact);
   return DLMPC_OK;
 }
 
@@ -575,16 +667,21 @@ int run_solve(dlmpc_problem *p, const double *x0_dev, const double *wpsi, const 
               double *u0_dev, double *phi_dev, dlmpc_stats *stats, double t_host0_ms) {
   std::string err;
   const int max_iter = p->opt.max_iter;
+  // cold starts without couplings: the compact form where setup chose it
+  const int compact = !wpsi && p->cp_a.empty() ? p->compact : 0;
+  const int sched = compact ? (compact == dlmpc::kCompactBlock ? 1 : 0) : p->sched;
+  hipGraphExec_t *exec = compact ? p->cgexec : p->gexec;
   API_HIP(hipEventRecord(p->ev_p0, p->stream));
-  int rc = p->eng->precompute(x0_dev, wpsi, wlam, max_iter, p->opt.eps, p->rho, err);
+  int rc = compact ? p->eng->compact_precompute(compact, x0_dev, max_iter, p->opt.eps, p->rho, err)
+                   : p->eng->precompute(x0_dev, wpsi, wlam, max_iter, p->opt.eps, p->rho, err);
   if (rc) return fail(rc, err);
   API_HIP(hipEventRecord(p->ev_p1, p->stream));
   API_HIP(hipEventRecord(p->ev_t0, p->stream));
   int launched = 0, launches = 0;
   bool stopped = false;
   Ctl *d_ctl = p->eng->ctl();
-  if (p->sched == 1) {
-    rc = p->eng->run_persistent(false, err);
+  if (sched == 1) {
+    rc = compact ? p->eng->compact_solve(err) : p->eng->run_persistent(false, err);
     if (rc) return fail(rc, err);
     launches = 1;
     stopped = true;
@@ -593,10 +690,10 @@ int run_solve(dlmpc_problem *p, const double *x0_dev, const double *wpsi, const 
   // read after every iteration; 4 also copies Phi through host memory between Phi-comp and
   // Psi-comp (the row-to-column exchange on the host, the other steps combined on the device),
   // 5 copies each kernel's results through host memory before the next kernel runs.
-  for (int it = 0; p->sched >= 3 && !stopped && it < max_iter; ++it) {
+  for (int it = 0; sched >= 3 && !stopped && it < max_iter; ++it) {
     for (int kk = 0; kk < 4; ++kk) {
       if ((rc = p->eng->launch_one(kk, err))) return fail(rc, err);
-      if ((p->sched == 5 || (p->sched == 4 && kk == 0)) && (rc = p->eng->host_exchange(kk, p->h_xchg, err)))
+      if ((sched == 5 || (sched == 4 && kk == 0)) && (rc = p->eng->host_exchange(kk, p->h_xchg, err)))
         return fail(rc, err);
     }
     ++launches;
@@ -610,9 +707,9 @@ int run_solve(dlmpc_problem *p, const double *x0_dev, const double *wpsi, const 
   // device-side stop and few host checks are needed. With check_every > 0 the chunk is fixed.
   ChunkPredictor pred;
   int n = p->K;
-  while (!stopped && p->sched == 0) {
+  while (!stopped && sched == 0) {
     n = std::max(1, std::min(n, max_iter - launched));
-    rc = launch_iterations(p, n);
+    rc = launch_graphs(exec, p->stream, n);
     if (rc) return rc;
     launched += n;
     ++launches;
@@ -630,6 +727,7 @@ int run_solve(dlmpc_problem *p, const double *x0_dev, const double *wpsi, const 
   }
   if (!stopped) return fail(DLMPC_EDEVICE, "the iteration did not reach its stop condition");
   API_HIP(hipEventRecord(p->ev_t1, p->stream));
+  if (compact && (rc = p->eng->compact_finish(compact, err))) return fail(rc, err);
   rc = p->eng->output(u0_dev, err);
   if (rc) return fail(rc, err);
   if (phi_dev) {
@@ -676,7 +774,7 @@ int run_solve(dlmpc_problem *p, const double *x0_dev, const double *wpsi, const 
     stats->objective = c.objective;
     stats->t_iter_ms = ms;
     stats->graph_launches = launches;  // host checks (graph and per-iteration schedules) or 1 (persistent)
-    stats->schedule = p->sched;
+    stats->schedule = sched;
     stats->start = wpsi ? DLMPC_START_STATE : DLMPC_START_COLD;
     stats->fell_back = 0;
     stats->t_warm_ms = 0.0;
@@ -794,7 +892,8 @@ int dlmpc_query(const dlmpc_problem *p, dlmpc_info *info) {
   info->factor_ms = h.factor_ms;
   info->factor_device = h.factor_where;
   info->factor_fallbacks = h.factor_fallbacks;
-  info->schedule = p->sched;
+  const int compact = p->cp_a.empty() ? p->compact : 0;  // couplings run the standard form
+  info->schedule = compact ? (compact == dlmpc::kCompactBlock ? 1 : 0) : p->sched;
   info->persistent_grid = (p->eng ? p->eng->persistent_grid() : 0);
   info->tune_graph_us = p->tune_graph_us;
   info->tune_persistent_us = p->tune_persistent_us;
@@ -806,7 +905,7 @@ int dlmpc_query(const dlmpc_problem *p, dlmpc_info *info) {
   for (int v = 0; v < 2; ++v) info->tune_phi_us[v] = p->tune_phi_us[v];
   for (int c = 0; c < 6; ++c) info->tune_psi_us[c] = p->tune_psi_us[c];
   info->tune_cached = p->tune_cached;
-  info->psi_structured = p->psi_structured ? 1 : 0;
+  info->psi_structured = compact ? compact == dlmpc::kCompactGlobal : p->psi_structured;
   info->tune_structured_us = p->tune_structured_us;
   info->sum_du_k = 0;
   for (int j = 0; j < h.N; ++j)

@@ -37,6 +37,7 @@ struct Ctl {
   double rho;          // single-instance engine: the penalty of the current solve
   int32_t inner_iters;  // single-instance engine: nested-ADMM iterations of the solve (couplings)
   uint32_t n_stop;      // batched engine: stopped instances counted by the current decision pass
+  int32_t c_phi, c_psi;  // compact single solves: the iteration in progress, the latest finished one
 };
 
 // Static work lists of the persistent schedule: block b runs Phi-comp for
@@ -158,7 +159,22 @@ class Engine {
   // max over columns of |N_j N_j' rho Lambda[:,c]| (Psi-step stationarity). Synchronises.
   virtual int certify(const double *x0_dev, double *out, std::string &err) = 0;
   virtual Ctl *ctl() = 0;
+  // Compact form of the iteration from the cold start (single_compact.h): which of kCompactDense
+  // (products with whole bases), kCompactGlobal (input rows and the plant's global recursions) and
+  // kCompactBlock (a whole solve in one workgroup) this problem allows, as a bit mask (1 << mode;
+  // negative: a status; builds their buffers on the first call); the per-solve set-up, one iteration (capturable), the
+  // decision that closes a chunk of iterations, a whole solve (kCompactBlock), and the expansion of
+  // the stopping iterate into Phi, Psi, Lambda and y.
+  virtual int compact_modes(std::string &err) = 0;
+  virtual int compact_precompute(int mode, const double *x0_dev, int max_iter, double eps, double rho,
+                                 std::string &err) = 0;
+  virtual int compact_iteration(int mode, std::string &err) = 0;
+  virtual int compact_decide(int mode, std::string &err) = 0;
+  virtual int compact_solve(std::string &err) = 0;
+  virtual int compact_finish(int mode, std::string &err) = 0;
 };
+
+constexpr int kCompactDense = 1, kCompactGlobal = 2, kCompactBlock = 3;
 
 std::unique_ptr<Engine> make_engine(int precision, int nx);
 

@@ -128,6 +128,10 @@ int factor_host(HostSetup &hs, std::string &err);
 // offsets come back to hs.off; the bases stay on the device in hs.d_nb.
 int factor_device(HostSetup &hs, int device, double chol_tol, std::string &err);
 
+// Growth of the plant over the horizon: largest |A^t v|_inf / |v|_inf over t < T and eight fixed sign
+// vectors v (the sum of squares of a row of A^t shows in every one of them).
+double plant_growth(const HostSetup &hs);
+
 // Releases hs.d_nb (no-op when null).
 void free_factors_device(HostSetup &hs);
 
