@@ -98,12 +98,29 @@ __global__ __launch_bounds__(256) void ws_gemm_kernel(GemmArgs g) {
   }
 }
 
-// db[g][n] = sum_s dZ[g][s][n]
-__global__ __launch_bounds__(256) void ws_bias_grad_kernel(const float *dZ, float *db, int S, int N) {
-  const int grp = blockIdx.y, n = blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
+// db[g][n] = sum_s dZ[g][s][n], 64 columns per block: the samples are dealt to the block's waves, eight
+// loads in flight per lane, and the waves' sums added in order. Bound by the latency of those loads:
+// one thread per column walks the S samples one load after another (64 columns of 200
+// samples, 64 subsystems: 42 us; here 3.1 us).
+constexpr int kBiasThreads = 1024;
+__global__ __launch_bounds__(kBiasThreads) void ws_bias_grad_kernel(const float *dZ, float *db, int S, int N) {
+  constexpr int W = kBiasThreads / 64;
+  __shared__ double part[W][64];
+  const int grp = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = blockIdx.x * 64 + lane;
+  const float *src = dZ + int64_t(grp) * S * N + min(n, N - 1);
   double s = 0.0;
-  for (int i = 0; i < S; ++i) s += dZ[(int64_t(grp) * S + i) * N + n];
+  for (int i = wave; i < S; i += 8 * W) {
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = src[int64_t(min(i + e * W, S - 1)) * N];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s += i + e * W < S ? double(x[e]) : 0.0;
+  }
+  part[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0 || n >= N) return;
+#pragma unroll
+  for (int w = 1; w < W; ++w) s += part[w][lane];
   db[int64_t(grp) * N + n] = float(s);
 }
 
@@ -340,7 +357,7 @@ int WarmStart::backward(int S, const double *y_dev, double *loss, std::string &e
   if ((rc = gemm<true, false, kStore>(stream_, G, LX, OUT, S, XA, dY, Mat{dW3, OUT, int64_t(LX) * OUT}, none,
                                       nullptr, err)))
     return rc;
-  hipLaunchKernelGGL(ws_bias_grad_kernel, dim3((OUT + 255) / 256, G), dim3(256), 0, stream_, dY_, db3, S, OUT);
+  hipLaunchKernelGGL(ws_bias_grad_kernel, dim3((OUT + 63) / 64, G), dim3(kBiasThreads), 0, stream_, dY_, db3, S, OUT);
   WS_CHECK(hipGetLastError());
   if ((rc = gemm<false, true, kGeluGrad>(stream_, G, S, H, OUT, dY, Mat{W3, OUT, int64_t(LX) * OUT}, dZ2, Z2,
                                          nullptr, err)))
@@ -349,7 +366,7 @@ int WarmStart::backward(int S, const double *y_dev, double *loss, std::string &e
   if ((rc = gemm<true, false, kStore>(stream_, G, H, H, S, A1, dZ2, Mat{dW2, H, int64_t(H) * H}, none, nullptr,
                                       err)))
     return rc;
-  hipLaunchKernelGGL(ws_bias_grad_kernel, dim3((H + 255) / 256, G), dim3(256), 0, stream_, dZ2_, db2, S, H);
+  hipLaunchKernelGGL(ws_bias_grad_kernel, dim3((H + 63) / 64, G), dim3(kBiasThreads), 0, stream_, dZ2_, db2, S, H);
   WS_CHECK(hipGetLastError());
   if ((rc = gemm<false, true, kGeluGrad>(stream_, G, S, H, H, dZ2, Mat{W2, H, int64_t(H) * H}, dZ1, Z1, nullptr,
                                          err)))
@@ -358,7 +375,7 @@ int WarmStart::backward(int S, const double *y_dev, double *loss, std::string &e
   if ((rc = gemm<true, false, kStore>(stream_, G, IN, H, S, X, dZ1, Mat{dW1, H, int64_t(IN) * H}, none, nullptr,
                                       err)))
     return rc;
-  hipLaunchKernelGGL(ws_bias_grad_kernel, dim3((H + 255) / 256, G), dim3(256), 0, stream_, dZ1_, db1, S, H);
+  hipLaunchKernelGGL(ws_bias_grad_kernel, dim3((H + 63) / 64, G), dim3(kBiasThreads), 0, stream_, dZ1_, db1, S, H);
   WS_CHECK(hipGetLastError());
   if (loss) {
     std::vector<double> part(kLossBlocks);
