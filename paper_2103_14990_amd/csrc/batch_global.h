@@ -7,9 +7,9 @@
 //   sum_j N_j W_j = [x; U],  U = sum_j N_u,j W_j,  x_0 = 0, x_t = A x_{t-1} + B U_{t-1};
 //   b = sum_c x0_c o_c is the trajectory from x(0) with the input rows b_u;
 //   N_j' alpha = N_u,j' g,  g_t = alpha_{u,t} + B' lam_{t+1},  lam_t = alpha_{x,t} + A' lam_{t+1},
-// with one g for all column subsystems. An iteration is four launches:
+// with one g for all column subsystems. An iteration is four launches (three on small networks):
 //   bsim_fwd_kernel    per instance: forward recursion and row update (alpha, s);
-//   bsim_adj_kernel    per instance: adjoint recursion (g);
+//   bsim_adj_kernel    per instance: adjoint recursion (g);   (bsim_both_kernel: both)
 //   bstep_kernel       per column subsystem: eta = N_u' g, tau, W = ||x0_j||^2 (tau + eta) and the
 //                      subsystem's own share N_u W of U, on the matrix cores in split bf16;
 //   bgather_kernel     U = sum of the shares per row subsystem, and the stopping decisions.
@@ -358,6 +358,167 @@ __global__ __launch_bounds__(kSimThreads) void bsim_adj_kernel(BArgs a) {
     if (t - 3 >= tl) step(t - 3, xa, xb, v[3]);
   }
   sum_parts();
+  lds_barrier();
+  for (int e = tid; e < NU; e += bd) a.gu[int64_t(b) * NU + e] = uv[e];
+}
+
+// Both recursions of one instance in one block, for networks whose rows of an instance fit on chip
+// (R floats; see kSimBothLds): forward recursion into LDS, the row update of all rows at once
+// from there, the adjoint recursion of the new alpha in place. ADMM iterations only; set-up passes
+// and iterations with streamed joins use the two kernels.
+// Bound by the chain of 2 T steps and four rounds of dependent loads; against the two kernels it saves
+// a launch, alpha's way through memory, and the parts' repeated recursion: 8 x 8 grid (T = 10, 5
+// instances) 9.1 + 9.6 -> 13.4 us, 16 x 16 boxed grid (T = 15, 64 instances) 15.9 + 11.6 -> 18.8 us.
+// Issuing the row data's loads ahead of the recursion, or all loads ahead of the stop check,
+// changed nothing.
+template <int NX, int RPT>
+__global__ __launch_bounds__(kSimThreads) void bsim_both_kernel(BArgs a) {
+  if (a.ctl->stop) return;
+  extern __shared__ __align__(16) float sim_lds[];
+  __shared__ double red[kSimThreads];
+  const int b = blockIdx.x, tid = threadIdx.x, bd = blockDim.x;
+  if (b >= a.ctl->batch || a.ictl[b].stop) return;
+  const int N = a.N, NS = N * NX, T = a.T, nu = a.nu, nuT = nu * (T - 1), NU = N * nuT, rs = a.rs;
+  const int64_t R = int64_t(N) * rs, plane = int64_t(a.Bmax) * R;
+  const bool warm = a.ctl->warm != 0;
+  const int it = a.ctl->iters + 1, cur = it & 1;
+  const bool cold1 = !warm && it == 1;
+  const float coef = warm ? 1.f : (it == 1 ? 0.f : (it == 2 ? 2.f : 1.f));
+  const bool use_u = warm || it >= 3;  // from a cold start tau = eta = 0 before iteration 3
+  float *y = sim_lds, *uv = y + T * NS;  // rows of the time steps [t][c][m], input rows [m][nuT]
+  RowEll<RPT> ell, elt;
+  ell.load(a.prp, a.pcol, a.pval, NS);
+  {
+    const float *us = a.usum + int64_t(b) * NU, *bs = a.bu + int64_t(b) * NU;
+    for (int e0 = tid; e0 < NU; e0 += 4 * bd) {  // eight loads in flight
+      float u[4], v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int e = min(e0 + q * bd, NU - 1);
+        u[q] = us[e];
+        v[q] = bs[e];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (e0 + q * bd < NU) {
+          float x = use_u ? u[q] : 0.f;
+          if (coef != 0.f) x += coef * v[q];
+          uv[e0 + q * bd] = x;
+        }
+    }
+  }
+  float bk[RPT][2], bc[RPT][NX][2];  // first two inputs of the state rows, of the subsystems tid + i bd
+  int ub[RPT], xi[RPT];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int r = min(tid + i * bd, NS - 1), c = r / N, m = r - c * N;
+    ub[i] = m * nuT;
+    xi[i] = m * NX + c;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      bk[i][k] = k < nu ? a.b_blk[int64_t(xi[i]) * nu + k] : 0.f;
+#pragma unroll
+      for (int q = 0; q < NX; ++q)
+        bc[i][q][k] = (k < nu && tid + i * bd < N) ? a.b_blk[(int64_t(tid + i * bd) * NX + q) * nu + k] : 0.f;
+    }
+    if (tid + i * bd < NS) y[r] = coef != 0.f ? coef * a.x0[int64_t(b) * NS + xi[i]] : 0.f;
+  }
+  elt.load(a.trp, a.tcol, a.tval, NS);
+  lds_barrier();
+  for (int t = 1; t < T; ++t) {
+    const float *src = y + (t - 1) * NS;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int r = tid + i * bd;
+      if (r < NS) {
+        float v = ell.dot(i, src, a.pcol, a.pval);
+        const float *u = uv + ub[i] + (t - 1) * nu;
+        v += bk[i][0] * u[0];
+        if (nu > 1) v += bk[i][1] * u[1];
+        for (int k = 2; k < nu; ++k) v += a.b_blk[int64_t(xi[i]) * nu + k] * u[k];
+        y[t * NS + r] = v;
+      }
+    }
+    lds_barrier();
+  }
+  // row update: thread (group g, subsystem m) takes the rows l = g, g + G, ... of m
+  const float rho = a.rho_b[b];
+  const float *ap0 = a.alpha + (cur ^ 1) * plane + b * R;
+  float *al0 = a.alpha + cur * plane + b * R, *s0 = a.s + b * R, *apz = a.alpha + (cur ^ 1) * plane + b * R;
+  const int G = bd / N, g = tid / N, m = tid - g * N;
+  double d = 0.0;
+  if (g < G) {
+    const float n = a.nrm[int64_t(b) * N + m];
+    for (int l0 = g; l0 < rs; l0 += 4 * G) {  // sixteen loads in flight
+      float ap[4], w[4], lo[4], hi[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int o = min(l0 + e * G, rs - 1) * N + m;
+        ap[e] = cold1 ? 0.f : ap0[o];
+        w[e] = a.wT[o];
+        lo[e] = a.lbT[o];
+        hi[e] = a.ubT[o];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int l = l0 + e * G;
+        if (l >= rs) break;
+        const int o = l * N + m;
+        float *p = l < NX * T ? y + o : uv + m * nuT + (l - NX * T);
+        const float av = *p - n * ap[e];
+        float sv, al;
+        if (n > 0.f) {
+          sv = rho * av / (rho + 2.f * w[e] * n);
+          sv = sv < lo[e] ? lo[e] : (sv > hi[e] ? hi[e] : sv);
+          al = (sv - av) / n;
+        } else {
+          sv = av;
+          al = 0.f;
+        }
+        al0[o] = al;
+        s0[o] = sv;
+        if (cold1) apz[o] = 0.f;
+        *p = al;
+        d += double(al - ap[e]) * double(al - ap[e]);
+      }
+    }
+  }
+  red[tid] = d;
+  lds_barrier();
+  if (tid < N) {
+    for (int q = 1; q < G; ++q) d += red[q * N + tid];
+    a.dlm[int64_t(b) * N + tid] = d;
+  }
+  if (cold1) return;  // alpha^1 = 0
+  const int tl = !warm && it == 2 ? 0 : 1;  // lam_0: offset terms of the second cold iteration
+  for (int t = T - 1; t >= tl; --t) {       // lam_t, then g_{t-1}
+    float *lam = y + t * NS;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int r = tid + i * bd;
+      if (r < NS) {
+        float v = lam[r];
+        if (t + 1 < T) v += elt.dot(i, lam + NS, a.tcol, a.tval);
+        lam[r] = v;
+        if (t == 0) a.lam0[int64_t(b) * NS + r] = v;
+      }
+    }
+    lds_barrier();
+    if (t == 0) break;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int mm = tid + i * bd;
+      if (mm >= N) break;
+      float *u = uv + mm * nuT + (t - 1) * nu;
+      for (int k = 0; k < nu; ++k) {
+        float x = u[k];
+#pragma unroll
+        for (int q = 0; q < NX; ++q)
+          x += (k < 2 ? (k == 0 ? bc[i][q][0] : bc[i][q][1]) : a.b_blk[(int64_t(mm) * NX + q) * nu + k]) * lam[q * N + mm];
+        u[k] = x;
+      }
+    }
+  }
   lds_barrier();
   for (int e = tid; e < NU; e += bd) a.gu[int64_t(b) * NU + e] = uv[e];
 }

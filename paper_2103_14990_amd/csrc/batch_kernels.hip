@@ -2128,10 +2128,13 @@ class BatchEngineT final : public BatchEngine {
   }
 
   int launch_one(int k, std::string &err) override {
-    if (glob_ && k == 0)
-      launch_fwd(args_);
-    else if (glob_ && k == 1) {
-      launch_adj(args_);
+    if (glob_ && k == 0) {
+      if (sim_both_)
+        launch_both(args_);
+      else
+        launch_fwd(args_);
+    } else if (glob_ && k == 1) {
+      if (!sim_both_) launch_adj(args_);
       BENG_CHECK(hipGetLastError());
       launch_step(args_);
     }
@@ -2149,14 +2152,19 @@ class BatchEngineT final : public BatchEngine {
 
   int iteration(std::string &err, bool joins) override {
     if (glob_) {
-      launch_fwd(args_);
-      BENG_CHECK(hipGetLastError());
-      if (joins) {  // the CG step of streamed joins sits between q = M p and the next projection
-        launch_cg_step(args_.Bmax, 1);
+      if (sim_both_ && !joins) {
+        launch_both(args_);
+        BENG_CHECK(hipGetLastError());
+      } else {
+        launch_fwd(args_);
+        BENG_CHECK(hipGetLastError());
+        if (joins) {  // the CG step of streamed joins sits between q = M p and the next projection
+          launch_cg_step(args_.Bmax, 1);
+          BENG_CHECK(hipGetLastError());
+        }
+        launch_adj(args_);
         BENG_CHECK(hipGetLastError());
       }
-      launch_adj(args_);
-      BENG_CHECK(hipGetLastError());
       launch_step(args_);
       BENG_CHECK(hipGetLastError());
       launch_gather(args_);
@@ -2431,6 +2439,7 @@ class BatchEngineT final : public BatchEngine {
     step_lds_ = size_t(16) * step_nt_ * per_inst;
     if (sim_start_lds_ > kGlobLds || step_lds_ > kGlobLds || plant_growth(hs) > kMaxGrowth) return DLMPC_OK;
     a.sim_q = std::max(1, std::min(kSimParts, 256 / a.Bmax));  // parts of the row update: a CU each
+    sim_both_ = N <= kSimThreads && sim_rpt() <= 2 && size_t(N) * hs.rs * sizeof(float) <= kSimBothLds;
     step_mt_ = (k32 / 16 + kStepWaves - 1) / kStepWaves;
     step_wn_ = (step_nt_ == 2 && k32 / 16 <= kStepWaves / 2) ? 2 : 1;
     // state rows c N + m of A and of A'
@@ -2528,6 +2537,20 @@ class BatchEngineT final : public BatchEngine {
       default: return go(bsim_adj_kernel<NX, 4>);
     }
   }
+  // Largest instance that takes bsim_both_kernel: at 45 KB (16 x 16 grid, T = 15, 64 instances) one
+  // block replaces 4 + 1 and wins, at 93 KB (667 nodes, T = 12, 23 instances: 11 + 1 blocks) the two
+  // are equal, 38 against 39 us, as the row update of one CU grows; past it the parts win.
+  static constexpr size_t kSimBothLds = 64 * 1024;
+  void launch_both(const BArgs &x) {
+    const int NS = hs_->N * NX;  // a thread per state row, and per four rows of the update
+    const dim3 t(std::min(kSimThreads, (std::max(NS, hs_->N * hs_->rs / 4) + 63) & ~63));
+    const size_t lds = size_t(hs_->N) * hs_->rs * sizeof(float);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(args_.Bmax), t, lds, stream_, x); };
+    switch (sim_rpt()) {
+      case 1: return go(bsim_both_kernel<NX, 1>);
+      default: return go(bsim_both_kernel<NX, 2>);
+    }
+  }
   void launch_sim_start(const int32_t *slots, int S, int pl) {
     auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(S), sim_threads(), sim_start_lds_, stream_, args_, slots, pl); };
     switch (sim_rpt()) {
@@ -2560,7 +2583,7 @@ class BatchEngineT final : public BatchEngine {
     const size_t lds = size_t(args_.Bw) * ((hs_->nu * (hs_->T - 1)) | 1) * sizeof(float);
     hipLaunchKernelGGL(bgather_kernel, dim3(hs_->N + args_.Bmax), dim3(256), lds, stream_, x);
   }
-  bool glob_ok_ = false, glob_ = false;
+  bool glob_ok_ = false, glob_ = false, sim_both_ = false;
   int step_nt_ = 1, step_mt_ = 1, step_wn_ = 1;
   size_t sim_lds_ = 0, sim_start_lds_ = 0, step_lds_ = 0;
   int nrt_ = 1, mtw_ = 1;
