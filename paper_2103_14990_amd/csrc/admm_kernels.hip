@@ -1009,27 +1009,36 @@ __global__ __launch_bounds__(kBlock) void persistent_kernel(KArgs<Tf> a, Sched s
 // ------------------------------------------------------------------ outputs
 
 // u(0) = the u_0 rows of Phi x0 (Algorithm 1: compute u(t) from Phi) and the FP64 objective
-// sum_r w_r y_r^2 at the stopping iterate. One workgroup.
+// sum_r w_r y_r^2 at the stopping iterate. One workgroup, so eight rows in flight per thread (45056
+// rows of the 1024-node mesh: 19 us FP64, 14 us FP32; 75 us with 256 threads and a row at a time).
+constexpr int kOutThreads = 1024;
 template <typename Tf, int NX>
-__global__ __launch_bounds__(kBlock) void output_kernel(KArgs<Tf> a, const double *w64, double *u0) {
-  __shared__ double red[kWaves];
+__global__ __launch_bounds__(kOutThreads) void output_kernel(KArgs<Tf> a, const double *w64, double *u0) {
+  __shared__ double red[kOutThreads / 64];
   const int tid = threadIdx.x;
   const int64_t ny = int64_t(a.N) * a.rs;
   double acc = 0.0;
-  for (int64_t i = tid; i < ny; i += kBlock) {
-    const double yv = double(a.y[i]);
-    acc += w64[i] * yv * yv;
+  for (int64_t i = tid; i < ny; i += 8 * kOutThreads) {
+    double yv[8], w[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int64_t o = min(i + e * kOutThreads, ny - 1);
+      yv[e] = double(a.y[o]);
+      w[e] = w64[o];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc += i + e * kOutThreads < ny ? w[e] * yv[e] * yv[e] : 0.0;
   }
   acc = wave_sum(acc);
   if ((tid & 63) == 0) red[tid >> 6] = acc;
   __syncthreads();
   if (tid == 0) {
     double s = 0.0;
-    for (int w = 0; w < kWaves; ++w) s += red[w];
+    for (int w = 0; w < kOutThreads / 64; ++w) s += red[w];
     a.ctl->objective = s;
   }
   const int nu = a.nu;
-  for (int i = tid; i < a.N * nu; i += kBlock) {
+  for (int i = tid; i < a.N * nu; i += kOutThreads) {
     const int m = i / nu, q = i - m * nu;
     u0[i] = double(a.y[int64_t(m) * a.rs + NX * a.T + q]);
   }
@@ -1066,105 +1075,148 @@ struct CertArgs {
   unsigned long long *out;  // [5] maxima as ordered bit patterns (all values >= 0)
 };
 
-// One block per subsystem b: Z_AB feasibility, |Phi - Psi| and Psi-step stationarity of column
-// block j = b, and the bound check of the rows of row subsystem m = b, all in FP64.
+// Two blocks per subsystem b, all in FP64: (b, 0) the Psi-step stationarity of column block j = b;
+// (b, 1) its Z_AB feasibility and |Phi - Psi|, and the bound check of the rows of row subsystem m = b.
+// Bound by latency, not by the two passes over the bases (0.5 GB each in FP64 on the 1024-node
+// mesh, d = 3, T = 15): hence eight basis vectors per wave and round, the parts side by side, loads
+// batched. There 530 us FP64 and 342 us FP32; 1307 and 1184 us as one block per subsystem with a
+// basis vector per wave at a time.
 template <typename Tf, int NX>
 __global__ __launch_bounds__(kBlock) void cert_kernel(KArgs<Tf> a, CertArgs c) {
   extern __shared__ double tk[];  // [NX][k_j]
-  __shared__ double red[kBlock / 64][NX + 4];
+  __shared__ double red[kBlock / 64][NX + 4], s_y[kBlock];
   const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rs = a.rs, T = a.T, nu = a.nu, ts = a.ts;
   double m_eq = 0.0, m_pf = 0.0, m_box = 0.0, m_stat = 0.0, s2[NX];
 #pragma unroll
   for (int q = 0; q < NX; ++q) s2[q] = 0.0;
-  // Z_AB Psi = I on the rows that can touch j's columns
-  const int64_t e0 = c.eq_ptr[j], e1 = c.eq_ptr[j + 1];
-  const int64_t per = int64_t(T) * NX * NX;
-  for (int64_t w = tid; w < (e1 - e0) * per; w += kBlock) {
-    const int64_t q = e0 + w / per;
-    const int rem = int(w % per), t = rem / (NX * NX), comp = (rem / NX) % NX, col = rem % NX;
-    const int i = c.eq_sub[q];
-    const int64_t ti = c.eq_tile[q];
-    double r = ti < 0 ? 0.0 : double(a.psi[ti * ts + (t * NX + comp) * NX + col]);
-    if (t == 0) {
-      if (i == j && comp == col) r -= 1.0;
-    } else {
-      for (int64_t n = c.eq_nptr[q]; n < c.eq_nptr[q + 1]; ++n) {
-        const int64_t tk_ = c.eq_ntile[n];
-        if (tk_ < 0) continue;
-        const double *A = c.a_blk + c.eq_ablk[n] * NX * NX;
-#pragma unroll
-        for (int cc = 0; cc < NX; ++cc) r -= A[comp * NX + cc] * double(a.psi[tk_ * ts + ((t - 1) * NX + cc) * NX + col]);
-      }
-      if (ti >= 0)
-        for (int u = 0; u < nu; ++u)
-          r -= c.b_blk[(int64_t(i) * NX + comp) * nu + u] * double(a.psi[ti * ts + (NX * T + (t - 1) * nu + u) * NX + col]);
-    }
-    m_eq = fmax(m_eq, fabs(r));
-  }
-  // Phi - Psi on j's support
   const int64_t t0 = a.tile_off[j], t1 = a.tile_off[j + 1];
-  for (int64_t e = tid; e < (t1 - t0) * ts; e += kBlock) {
-    const int64_t idx = t0 * ts + e;
-    const double d = double(a.phi[idx]) - double(a.psi[idx]);
-    m_pf = fmax(m_pf, fabs(d));
-    s2[e % NX] += d * d;
-  }
-  // N_j N_j' (rho Lambda_c): coordinates first, then the rows
-  const int D = int(t1 - t0) * rs, ld = (D + 3) & ~3, k = a.kdim[j];
-  const Tf *Nj = a.nb + a.nb_off[j];
-  const double rho = a.ctl->rho;
-  // one wave per basis vector i: lanes over the rows (coalesced column reads), wave reduction
-  for (int i = wave; i < k; i += kBlock / 64) {
-    double acc[NX];
+  if (blockIdx.y == 0) {
+    // N_j N_j' (rho Lambda_c): coordinates first, then the rows
+    const int D = int(t1 - t0) * rs, ld = (D + 3) & ~3, k = a.kdim[j];
+    const Tf *Nj = a.nb + a.nb_off[j], *lam = a.lam + t0 * ts;
+    const double rho = a.ctl->rho;
+    // eight basis vectors per wave: lanes over the rows (coalesced column reads), wave reduction
+    for (int i0 = 8 * wave; i0 < k; i0 += 8 * (kBlock / 64)) {
+      double acc[NX][8];
 #pragma unroll
-    for (int col = 0; col < NX; ++col) acc[col] = 0.0;
-    for (int r = lane; r < D; r += 64) {
-      const double n = double(Nj[int64_t(i) * ld + r]);
+      for (int col = 0; col < NX; ++col)
 #pragma unroll
-      for (int col = 0; col < NX; ++col) acc[col] += n * rho * double(a.lam[t0 * ts + int64_t(r) * NX + col]);
+        for (int e = 0; e < 8; ++e) acc[col][e] = 0.0;
+      for (int r = lane; r < D; r += 64) {
+        Tf n[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) n[e] = Nj[int64_t(min(i0 + e, k - 1)) * ld + r];
+#pragma unroll
+        for (int col = 0; col < NX; ++col) {
+          const double l = rho * double(lam[int64_t(r) * NX + col]);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[col][e] += double(n[e]) * l;
+        }
+      }
+      const int i = i0 + ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
+#pragma unroll
+      for (int col = 0; col < NX; ++col) {
+        const double v = wave_sum8(acc[col], lane);
+        if ((lane & 7) == 0 && i < k) tk[col * k + i] = v;
+      }
     }
+    __syncthreads();
+    // rows over the threads (consecutive rows, consecutive addresses), eight basis vectors in flight
+    for (int r = tid; r < D; r += kBlock) {
+      double acc[NX];
 #pragma unroll
-    for (int col = 0; col < NX; ++col) {
-      double v = acc[col];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-      if (lane == 0) tk[col * k + i] = v;
+      for (int col = 0; col < NX; ++col) acc[col] = 0.0;
+      int i = 0;
+      for (; i + 8 <= k; i += 8) {
+        Tf n[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) n[u] = Nj[int64_t(i + u) * ld + r];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int col = 0; col < NX; ++col) acc[col] += double(n[u]) * tk[col * k + i + u];
+      }
+      for (; i < k; ++i)
+#pragma unroll
+        for (int col = 0; col < NX; ++col) acc[col] += double(Nj[int64_t(i) * ld + r]) * tk[col * k + i];
+#pragma unroll
+      for (int col = 0; col < NX; ++col) m_stat = fmax(m_stat, fabs(acc[col]));
     }
-  }
-  __syncthreads();
-  // rows over the threads (consecutive rows, consecutive addresses), four basis vectors in flight
-  for (int r = tid; r < D; r += kBlock) {
-    double acc[NX];
+  } else {
+    // Z_AB Psi = I on the rows that can touch j's columns
+    const int64_t e0 = c.eq_ptr[j];
+    const int ne = int(c.eq_ptr[j + 1] - e0);
+    const unsigned per = unsigned(T) * NX * NX;
+    for (unsigned w = tid; w < unsigned(ne) * per; w += kBlock) {
+      const unsigned rem = w % per, t = rem / (NX * NX), comp = (rem / NX) % NX, col = rem % NX;
+      const int64_t q = e0 + w / per;
+      const int i = c.eq_sub[q];
+      const int64_t ti = c.eq_tile[q];
+      double r = ti < 0 ? 0.0 : double(a.psi[ti * ts + (t * NX + comp) * NX + col]);
+      if (t == 0) {
+        if (i == j && comp == col) r -= 1.0;
+      } else {
+        const int64_t n1 = c.eq_nptr[q + 1];
+        for (int64_t n = c.eq_nptr[q]; n < n1; n += 4) {  // four neighbours in flight
+          int64_t tn[4];
+          double A[4][NX], x[4][NX];
 #pragma unroll
-    for (int col = 0; col < NX; ++col) acc[col] = 0.0;
-    int i = 0;
-    for (; i + 4 <= k; i += 4) {
-      double n[4];
+          for (int e = 0; e < 4; ++e) tn[e] = c.eq_ntile[min(n + e, n1 - 1)];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) n[u] = double(Nj[int64_t(i + u) * ld + r]);
+          for (int e = 0; e < 4; ++e) {
+            const double *blk = c.a_blk + c.eq_ablk[min(n + e, n1 - 1)] * NX * NX + comp * NX;
+            const Tf *src = a.psi + (tn[e] < 0 ? 0 : tn[e]) * ts + (t - 1) * NX * NX + col;
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+            for (int cc = 0; cc < NX; ++cc) {
+              A[e][cc] = blk[cc];
+              x[e][cc] = double(src[cc * NX]);
+            }
+          }
 #pragma unroll
-        for (int col = 0; col < NX; ++col) acc[col] += n[u] * tk[col * k + i + u];
+          for (int e = 0; e < 4; ++e)
+            if (n + e < n1 && tn[e] >= 0)
+#pragma unroll
+              for (int cc = 0; cc < NX; ++cc) r -= A[e][cc] * x[e][cc];
+        }
+        if (ti >= 0)
+          for (int u = 0; u < nu; ++u)
+            r -= c.b_blk[(int64_t(i) * NX + comp) * nu + u] *
+                 double(a.psi[ti * ts + (NX * T + (t - 1) * nu + u) * NX + col]);
+      }
+      m_eq = fmax(m_eq, fabs(r));
     }
-    for (; i < k; ++i)
+    // Phi - Psi on j's support, a row (NX columns) per thread
+    const Tf *ph = a.phi + t0 * ts, *ps = a.psi + t0 * ts;
+    for (int r = tid; r < int(t1 - t0) * rs; r += kBlock)
 #pragma unroll
-      for (int col = 0; col < NX; ++col) acc[col] += double(Nj[int64_t(i) * ld + r]) * tk[col * k + i];
+      for (int q = 0; q < NX; ++q) {
+        const double d = double(ph[int64_t(r) * NX + q]) - double(ps[int64_t(r) * NX + q]);
+        m_pf = fmax(m_pf, fabs(d));
+        s2[q] += d * d;
+      }
+    // bounds of row subsystem m = j: y = Phi x0 recomputed from the tiles of m's row, the tiles dealt
+    // to the groups of rs threads
+    const int m = j;
+    for (int l0 = 0; l0 < rs; l0 += kBlock) {
+      const int rl = min(rs - l0, kBlock), G = kBlock / rl, g = tid / rl, l = l0 + tid - g * rl;
+      double y = 0.0;
+      if (g < G)
+        for (int64_t q = a.rt_ptr[m] + g; q < a.rt_ptr[m + 1]; q += G) {
+          const int64_t tile = a.rt_tile[q];
+          const int jj = a.rt_col[q];
 #pragma unroll
-    for (int col = 0; col < NX; ++col) m_stat = fmax(m_stat, fabs(acc[col]));
-  }
-  // bounds of row subsystem m = j: y = Phi x0 recomputed from the tiles of m's row
-  const int m = j;
-  for (int l = tid; l < rs; l += kBlock) {
-    double y = 0.0;
-    for (int64_t q = a.rt_ptr[m]; q < a.rt_ptr[m + 1]; ++q) {
-      const int64_t tile = a.rt_tile[q];
-      const int jj = a.rt_col[q];
-#pragma unroll
-      for (int cc = 0; cc < NX; ++cc) y += double(a.phi[tile * ts + int64_t(l) * NX + cc]) * c.x0[jj * NX + cc];
+          for (int cc = 0; cc < NX; ++cc) y += double(a.phi[tile * ts + int64_t(l) * NX + cc]) * c.x0[jj * NX + cc];
+        }
+      __syncthreads();
+      s_y[tid] = y;
+      __syncthreads();
+      if (tid < rl) {
+        for (int q = 1; q < G; ++q) y += s_y[q * rl + tid];
+        const double lbv = double(a.lb[int64_t(m) * rs + l]), ubv = double(a.ub[int64_t(m) * rs + l]);
+        m_box = fmax(m_box, fmax(lbv - y, y - ubv));
+      }
     }
-    const double lbv = double(a.lb[int64_t(m) * rs + l]), ubv = double(a.ub[int64_t(m) * rs + l]);
-    m_box = fmax(m_box, fmax(lbv - y, y - ubv));
   }
   // block maxima and column sums, then the device maxima
   auto wmax = [](double v) {
@@ -1669,7 +1721,7 @@ class EngineT final : public Engine {
   }
 
   int output(double *u0_dev, std::string &err) override {
-    hipLaunchKernelGGL((output_kernel<Tf, NX>), dim3(1), dim3(kBlock), 0, stream_, args_, w64_, u0_dev);
+    hipLaunchKernelGGL((output_kernel<Tf, NX>), dim3(1), dim3(kOutThreads), 0, stream_, args_, w64_, u0_dev);
     ENG_CHECK(hipGetLastError());
     return DLMPC_OK;
   }
@@ -1688,7 +1740,7 @@ class EngineT final : public Engine {
     ENG_CHECK(hipMemsetAsync(cert_out_, 0, 5 * sizeof(unsigned long long), stream_));
     c.out = cert_out_;
     const size_t lds = size_t(NX) * std::max(hs_->k_max, 1) * sizeof(double);
-    hipLaunchKernelGGL((cert_kernel<Tf, NX>), dim3(hs_->N), dim3(kBlock), lds, stream_, args_, c);
+    hipLaunchKernelGGL((cert_kernel<Tf, NX>), dim3(hs_->N, 2), dim3(kBlock), lds, stream_, args_, c);
     ENG_CHECK(hipGetLastError());
     unsigned long long h[5];
     ENG_CHECK(hipMemcpyAsync(h, cert_out_, sizeof(h), hipMemcpyDeviceToHost, stream_));
