@@ -17,7 +17,7 @@
 // iteration (1.03 GB at d = 3, T = 15 on the 1024-node mesh); the input rows alone are 14 of 44
 // there, and W_j is no longer re-read by every row subsystem of the patch.
 // Measured per iteration, 64 instances of that mesh: 496 us through the dense products (bphi 221, bpsi
-// 267, bdecide 8), 247 us here (30 + 25 + 171 + 21); 64 of the 16 x 16 boxed grid 63 -> 46 us.
+// 267, bdecide 8), 253 us here (32 + 27 + 174 + 20); 64 of the 16 x 16 boxed grid 63 -> 43 us.
 // The recursions run in FP32; products accumulate over fewer rows, so the iterate is closer to
 // the FP64 one than through the dense bases (u(0) after 50 iterations on the 16 x 16 boxed grid:
 // 6e-7 against 2e-6 relative). A plant whose A^t grows over the horizon amplifies the rounding of
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(kSimThreads) void bsim_adj_kernel(BArgs a) {
 // and iterations with streamed joins use the two kernels.
 // Bound by the chain of 2 T steps and four rounds of dependent loads; against the two kernels it saves
 // a launch, alpha's way through memory, and the parts' repeated recursion: 8 x 8 grid (T = 10, 5
-// instances) 9.1 + 9.6 -> 13.4 us, 16 x 16 boxed grid (T = 15, 64 instances) 15.9 + 11.6 -> 18.8 us.
+// instances) 9.1 + 9.6 -> 13.4 us, 16 x 16 boxed grid (T = 10, 64 instances) 15.9 + 11.6 -> 18.8 us.
 // Issuing the row data's loads ahead of the recursion, or all loads ahead of the stop check,
 // changed nothing.
 template <int NX, int RPT>

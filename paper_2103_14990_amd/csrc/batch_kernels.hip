@@ -2537,7 +2537,7 @@ class BatchEngineT final : public BatchEngine {
       default: return go(bsim_adj_kernel<NX, 4>);
     }
   }
-  // Largest instance that takes bsim_both_kernel: at 45 KB (16 x 16 grid, T = 15, 64 instances) one
+  // Largest instance that takes bsim_both_kernel: at 30 KB (16 x 16 grid, T = 10, 64 instances) one
   // block replaces 4 + 1 and wins, at 93 KB (667 nodes, T = 12, 23 instances: 11 + 1 blocks) the two
   // are equal, 38 against 39 us, as the row update of one CU grows; past it the parts win.
   static constexpr size_t kSimBothLds = 64 * 1024;

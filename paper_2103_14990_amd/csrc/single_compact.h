@@ -304,7 +304,7 @@ __device__ __forceinline__ Tf wave_sum8(const Tf *x, int lane) {
 // per lane of its kUC basis vectors in registers, so an iteration reads the bases once for both
 // products (the rows past them twice, the second time from the L2).
 // Bound by the bytes of the bases on large networks, by latency on small ones. Input rows of the
-// 1024-node mesh (d = 3, T = 15): 36 us FP32, 81 us FP64 (5.2 and 4.6 TB/s); with all rows in
+// 1024-node mesh (d = 3, T = 15; 41 M entries): 36 us FP32, 81 us FP64 (4.8 and 4.2 TB/s); with all rows in
 // registers (four vectors, half the waves) 57 and 79 us; as two kernels that each read the bases
 // 56 + 41 and 94 + 66 us.
 template <typename Tf, int NX>
