@@ -27,6 +27,7 @@
 #include <vector>
 #include <cstring>
 #include <memory>
+#include <new>
 #include <string>
 
 #include "dlmpc_device.h"
@@ -1795,8 +1796,19 @@ class EngineT final : public Engine {
 
   int compact_modes(std::string &err) override {
     if (cmodes_ < 0) {
-      const int rc = build_compact(err);
-      if (rc) return rc;
+      int rc;
+      try {
+        rc = build_compact(err);
+      } catch (const std::bad_alloc &) {
+        rc = DLMPC_ENOMEM;
+      }
+      if (rc == DLMPC_ENOMEM) {  // no memory for it: the standard form, which needs none of this
+        (void)hipGetLastError();
+        err.clear();
+        cmodes_ = 0;
+      } else if (rc) {
+        return rc;
+      }
     }
     return cmodes_;
   }

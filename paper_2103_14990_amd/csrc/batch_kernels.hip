@@ -1963,7 +1963,12 @@ class BatchEngineT final : public BatchEngine {
     a.rb = 1;
     a.rm = int64_t(hs.rs) * bmax;
     a.rl = bmax;
-    if ((rc = init_global(err))) return rc;
+    if ((rc = init_global(err)) == DLMPC_ENOMEM) {  // no memory for it: the dense products
+      (void)hipGetLastError();
+      err.clear();
+    } else if (rc) {
+      return rc;
+    }
     a.phi_mode = 0;
     a.src = nullptr;
     a.dst_k = nullptr;
