@@ -30,6 +30,7 @@
 #include <new>
 #include <string>
 
+#include "device_buffers.h"
 #include "dlmpc_device.h"
 
 namespace dlmpc {
@@ -1522,6 +1523,16 @@ class EngineT final : public Engine {
       structured_ = true;
       return DLMPC_OK;
     }
+    bool have = false;
+    const int rc = build_optional(smem_, [&] { return build_structured(err); }, &have, err);
+    if (!rc && !have) {
+      err = "no memory for the structured Psi-comp";
+      return DLMPC_ENOMEM;
+    }
+    return rc;
+  }
+
+  int build_structured(std::string &err) {
     const HostSetup &hs = *hs_;
     const int N = hs.N, nx = hs.nx, nu = hs.nu, T = hs.T;
     const int nuT = nu * (T - 1);
@@ -1583,12 +1594,12 @@ class EngineT final : public Engine {
     SimArgs<Tf> x{};
     int rc;
     Tf *nbu = nullptr;
-    if ((rc = upload(nbu_off, &x.nbu_off, err)) || (rc = alloc(&nbu, size_t(nbu_off[N]), err)) ||
-        (rc = upload(rp0, &x.rp0, err)) || (rc = upload(rp, &x.rp, err)) || (rc = upload(rpt, &x.rpt, err)) ||
-        (rc = upload(e0, &x.e0, err)) || (rc = upload(col, &x.col, err)) || (rc = upload(colt, &x.colt, err)) ||
-        (rc = upload(val, &x.val, err)) || (rc = upload(valt, &x.valt, err)) || (rc = upload(bb, &x.bblk, err)) ||
-        (rc = upload(hs.tile_rsub, &x.tile_sub, err)) || (rc = upload(goff, &x.goff, err)) ||
-        (rc = alloc(&x.g, size_t(goff[N]), err)))
+    if ((rc = upload(nbu_off, &x.nbu_off, err, smem_)) || (rc = smem_.alloc(&nbu, size_t(nbu_off[N]), err)) ||
+        (rc = upload(rp0, &x.rp0, err, smem_)) || (rc = upload(rp, &x.rp, err, smem_)) || (rc = upload(rpt, &x.rpt, err, smem_)) ||
+        (rc = upload(e0, &x.e0, err, smem_)) || (rc = upload(col, &x.col, err, smem_)) || (rc = upload(colt, &x.colt, err, smem_)) ||
+        (rc = upload(val, &x.val, err, smem_)) || (rc = upload(valt, &x.valt, err, smem_)) || (rc = upload(bb, &x.bblk, err, smem_)) ||
+        (rc = upload(hs.tile_rsub, &x.tile_sub, err, smem_)) || (rc = upload(goff, &x.goff, err, smem_)) ||
+        (rc = smem_.alloc(&x.g, size_t(goff[N]), err)))
       return rc;
     x.nbu = nbu;
     hipLaunchKernelGGL(gather_nu_kernel<Tf>, dim3(N), dim3(kBlock), 0, stream_, args_, x);
@@ -1596,7 +1607,7 @@ class EngineT final : public Engine {
     ENG_CHECK(hipStreamSynchronize(stream_));
     spu_ = pu_;
     spu_.max_units = 1;
-    if ((rc = alloc(&spu_.part, size_t(N) * 2 * NX, err))) return rc;
+    if ((rc = smem_.alloc(&spu_.part, size_t(N) * 2 * NX, err))) return rc;
     ENG_CHECK(hipMemset(spu_.part, 0, sizeof(double) * size_t(N) * 2 * NX));
     sa_ = x;
     lds_s1_ = lds1;
@@ -1794,23 +1805,42 @@ class EngineT final : public Engine {
 
   Ctl *ctl() override { return args_.ctl; }
 
-  int compact_modes(std::string &err) override {
-    if (cmodes_ < 0) {
-      int rc;
-      try {
-        rc = build_compact(err);
-      } catch (const std::bad_alloc &) {
-        rc = DLMPC_ENOMEM;
-      }
-      if (rc == DLMPC_ENOMEM) {  // no memory for it: the standard form, which needs none of this
-        (void)hipGetLastError();
-        err.clear();
-        cmodes_ = 0;
-      } else if (rc) {
-        return rc;
-      }
+  int compact_modes(int want, std::string &err) override {
+    const int dense = 1 << kCompactDense | 1 << kCompactBlock, glob = 1 << kCompactGlobal;
+    // 32-bit offsets: of the tiles' rows in the bases, and in the shares
+    if (hs_->nb_off[hs_->N] >= (int64_t(1) << 32)) return 0;
+    cmem_.give_back();
+    cdmem_.give_back();
+    cgmem_.give_back();
+    CArgs<Tf> c{};
+    bool have = false;
+    int rc = build_optional(cmem_, [&] { return build_compact(&c, err); }, &have, err);
+    if (rc || !have) return rc;
+    int modes = 0;
+    if (want & dense) {
+      cd_ = c;
+      rc = build_optional(cdmem_, [&] { return build_compact_dense(&modes, err); }, &have, err);
+      if (rc) return rc;
+      if (!have) modes = 0;
     }
-    return cmodes_;
+    if (want & glob) {
+      int m = 0;
+      cg_ = c;
+      rc = build_optional(cgmem_, [&] { return build_compact_global(&m, err); }, &have, err);
+      if (rc) return rc;
+      if (have) modes |= m;
+    }
+    return modes & want;
+  }
+
+  void settle(int mode, bool structured) override {
+    if (mode != kCompactDense && mode != kCompactBlock) cdmem_.give_back();
+    if (mode != kCompactGlobal) cgmem_.give_back();
+    if (mode == 0) cmem_.give_back();
+    if (mode != kCompactGlobal && !structured) {
+      smem_.give_back();
+      struct_ready_ = structured_ = false;
+    }
   }
 
   int compact_precompute(int mode, const double *x0_dev, int max_iter, double eps, double rho,
@@ -1864,30 +1894,22 @@ class EngineT final : public Engine {
     return DLMPC_OK;
   }
 
-  ~EngineT() override {
-    for (void *p : owned_) (void)hipFree(p);
-  }
-
  private:
   static constexpr size_t kMaxLds = 64 * 1024;
 
   template <typename U>
   int alloc(U **dst, size_t n, std::string &err) {
-    void *p = nullptr;
-    const size_t bytes = std::max<size_t>(n, 1) * sizeof(U);
-    if (hipMalloc(&p, bytes) != hipSuccess) {
-      err = "hipMalloc of " + std::to_string(bytes) + " bytes failed";
-      return DLMPC_ENOMEM;
-    }
-    owned_.push_back(p);
-    *dst = static_cast<U *>(p);
-    return DLMPC_OK;
+    return mem_.alloc(dst, n, err);
   }
   template <typename U, typename V>
   int upload(const std::vector<U> &src, V **dst, std::string &err) {
+    return upload(src, dst, err, mem_);
+  }
+  template <typename U, typename V>
+  int upload(const std::vector<U> &src, V **dst, std::string &err, DeviceBuffers &mem) {
     static_assert(sizeof(U) == sizeof(V), "upload type");
     U *p = nullptr;
-    int rc = alloc(&p, src.size(), err);
+    int rc = mem.alloc(&p, src.size(), err);
     if (rc) return rc;
     if (!src.empty()) ENG_CHECK(hipMemcpy(p, src.data(), src.size() * sizeof(U), hipMemcpyHostToDevice));
     *dst = reinterpret_cast<V *>(p);
@@ -1935,19 +1957,12 @@ class EngineT final : public Engine {
       pick(std::integral_constant<int, 2>{});
   }
 
-  int build_compact(std::string &err) {
+  // What every compact form holds.
+  int build_compact(CArgs<Tf> *out, std::string &err) {
     const HostSetup &hs = *hs_;
-    const int N = hs.N, NS = N * NX, nuT = hs.nu * (hs.T - 1), rs = hs.rs;
+    const int N = hs.N, rs = hs.rs;
     const int64_t R = int64_t(N) * rs, K = hs.sum_k;
-    int rc, modes = 0;
-    // 32-bit offsets: of the tiles' rows in the bases, and in the shares
-    if (hs.nb_off[N] >= (int64_t(1) << 32)) {
-      cmodes_ = 0;
-      return DLMPC_OK;
-    }
     CArgs<Tf> c{};
-    std::vector<int64_t> koff(N + 1, 0);
-    for (int j = 0; j < N; ++j) koff[j + 1] = koff[j] + hs.kdim[j];
     std::vector<double> on2(size_t(N) * NX, 0.0);
     for (int j = 0; j < N; ++j) {
       const int D = int(hs.patch[j].size()) * rs, ld = padded_ld(D);
@@ -1957,58 +1972,78 @@ class EngineT final : public Engine {
           on2[size_t(j) * NX + q] += o * o;
         }
     }
-    if ((rc = upload(koff, &c.koff, err)) || (rc = upload(on2, &c.on2, err)) ||
-        (rc = upload(hs.tile_rsub, &c.rsub, err)) || (rc = alloc(&c.al, size_t(3 * R), err)) ||
-        (rc = alloc(&c.s, size_t(2 * R), err)) || (rc = alloc(&c.bv, size_t(R), err)) ||
-        (rc = alloc(&c.tau, size_t(K), err)) || (rc = alloc(&c.eta, size_t(K), err)) ||
-        (rc = alloc(&c.v, size_t(2 * K), err)) || (rc = alloc(&c.xn, size_t(N), err)) ||
-        (rc = alloc(&c.dlq, size_t(N) * (1 + kCParts), err)) || (rc = alloc(&c.sdl, size_t(N), err)) ||
-        (rc = alloc(&c.od, size_t(N) * NX, err)))
+    int rc;
+    DeviceBuffers &m = cmem_;
+    if ((rc = upload(k_offsets(), &c.koff, err, m)) || (rc = upload(on2, &c.on2, err, m)) ||
+        (rc = upload(hs.tile_rsub, &c.rsub, err, m)) || (rc = m.alloc(&c.al, size_t(3 * R), err)) ||
+        (rc = m.alloc(&c.s, size_t(2 * R), err)) || (rc = m.alloc(&c.bv, size_t(R), err)) ||
+        (rc = m.alloc(&c.tau, size_t(K), err)) || (rc = m.alloc(&c.eta, size_t(K), err)) ||
+        (rc = m.alloc(&c.v, size_t(2 * K), err)) || (rc = m.alloc(&c.xn, size_t(N), err)) ||
+        (rc = m.alloc(&c.dlq, size_t(N) * (1 + kCParts), err)) || (rc = m.alloc(&c.sdl, size_t(N), err)) ||
+        (rc = m.alloc(&c.od, size_t(N) * NX, err)))
       return rc;
-    // units of basis vectors (those of one subsystem consecutive) and row-side tiles
-    auto lists = [&](CArgs<Tf> &x, int rows, const std::vector<int64_t> &boff) {
-      std::vector<CUnit> unit;
-      std::vector<int32_t> ufirst(N + 1, 0);
-      std::vector<CTile> ct(size_t(hs.n_tiles));
-      for (int64_t q = 0; q < hs.n_tiles; ++q) {
+    *out = c;
+    return DLMPC_OK;
+  }
+
+  std::vector<int64_t> k_offsets() const {
+    std::vector<int64_t> koff(hs_->N + 1, 0);
+    for (int j = 0; j < hs_->N; ++j) koff[j + 1] = koff[j] + hs_->kdim[j];
+    return koff;
+  }
+
+  // Units of basis vectors (those of one subsystem consecutive) and row-side tiles of a form whose
+  // products read `rows` rows per subsystem, from bases at boff.
+  int compact_lists(CArgs<Tf> &x, int rows, const std::vector<int64_t> &boff, DeviceBuffers &mem, std::string &err) {
+    const HostSetup &hs = *hs_;
+    const int N = hs.N;
+    const std::vector<int64_t> koff = k_offsets();
+    std::vector<CUnit> unit;
+    std::vector<int32_t> ufirst(N + 1, 0);
+    std::vector<CTile> ct(size_t(hs.n_tiles));
+    for (int64_t q = 0; q < hs.n_tiles; ++q) {
+      const int j = hs.rt_col[q];
+      ct[q] = {uint32_t(boff[j] + (hs.rt_tile[q] - hs.tile_off[j]) * rows),
+               padded_ld(int(hs.patch[j].size()) * rows), hs.kdim[j], int32_t(koff[j]), j, 0};
+    }
+    int64_t so = 0;
+    for (int j = 0; j < N; ++j) {
+      ufirst[j] = int32_t(unit.size());
+      for (int i0 = 0; i0 < std::max(hs.kdim[j], 1); i0 += kP1Cols) {
+        unit.push_back({j, i0, int32_t(hs.patch[j].size()), hs.kdim[j], hs.tile_off[j], boff[j], koff[j], so});
+        so += padded_ld(int(hs.patch[j].size()) * rows);
+      }
+    }
+    ufirst[N] = int32_t(unit.size());
+    std::vector<int32_t> sptr(N + 1, 0);
+    std::vector<uint32_t> soff;
+    for (int m = 0; m < N; ++m) {
+      for (int64_t q = hs.rt_ptr[m]; q < hs.rt_ptr[m + 1]; ++q) {
         const int j = hs.rt_col[q];
-        ct[q] = {uint32_t(boff[j] + (hs.rt_tile[q] - hs.tile_off[j]) * rows),
-                 padded_ld(int(hs.patch[j].size()) * rows), hs.kdim[j], int32_t(koff[j]), j, 0};
+        for (int u = ufirst[j]; u < ufirst[j + 1]; ++u)
+          soff.push_back(uint32_t(unit[u].so + (hs.rt_tile[q] - hs.tile_off[j]) * rows));
       }
-      int64_t so = 0;
-      for (int j = 0; j < N; ++j) {
-        ufirst[j] = int32_t(unit.size());
-        for (int i0 = 0; i0 < std::max(hs.kdim[j], 1); i0 += kP1Cols) {
-          unit.push_back({j, i0, int32_t(hs.patch[j].size()), hs.kdim[j], hs.tile_off[j], boff[j], koff[j], so});
-          so += padded_ld(int(hs.patch[j].size()) * rows);
-        }
-      }
-      ufirst[N] = int32_t(unit.size());
-      std::vector<int32_t> sptr(N + 1, 0);
-      std::vector<uint32_t> soff;
-      for (int m = 0; m < N; ++m) {
-        for (int64_t q = hs.rt_ptr[m]; q < hs.rt_ptr[m + 1]; ++q) {
-          const int j = hs.rt_col[q];
-          for (int u = ufirst[j]; u < ufirst[j + 1]; ++u)
-            soff.push_back(uint32_t(unit[u].so + (hs.rt_tile[q] - hs.tile_off[j]) * rows));
-        }
-        sptr[m + 1] = int32_t(soff.size());
-      }
-      x.rows = rows;
-      x.n_units = ufirst[N];
-      int q;
-      if ((q = upload(unit, &x.unit, err)) || (q = upload(ufirst, &x.ufirst, err)) || (q = upload(ct, &x.ct, err)) ||
-          (q = upload(boff, &x.boff, err)) ||
-          (q = upload(sptr, &x.sptr, err)) || (q = upload(soff, &x.soff, err)) ||
-          (q = alloc(&x.share, size_t(so), err)) || (q = alloc(&x.part, size_t(2) * ufirst[N], err)))
-        return q;
-      return 0;
-    };
-    cd_ = c;
+      sptr[m + 1] = int32_t(soff.size());
+    }
+    x.rows = rows;
+    x.n_units = ufirst[N];
+    int q;
+    if ((q = upload(unit, &x.unit, err, mem)) || (q = upload(ufirst, &x.ufirst, err, mem)) ||
+        (q = upload(ct, &x.ct, err, mem)) || (q = upload(boff, &x.boff, err, mem)) ||
+        (q = upload(sptr, &x.sptr, err, mem)) || (q = upload(soff, &x.soff, err, mem)) ||
+        (q = mem.alloc(&x.share, size_t(so), err)) || (q = mem.alloc(&x.part, size_t(2) * ufirst[N], err)))
+      return q;
+    return DLMPC_OK;
+  }
+
+  // Whole bases, and everything in one workgroup: what fits of the two goes to *modes.
+  int build_compact_dense(int *modes, std::string &err) {
+    const HostSetup &hs = *hs_;
+    const int N = hs.N, rs = hs.rs;
+    const int64_t R = int64_t(N) * rs, K = hs.sum_k;
     cd_.basis = args_.nb;
-    if ((rc = lists(cd_, rs, hs.nb_off))) return rc;
     cstep_lds_[0] = size_t(padded_ld(hs.d_col_max)) * sizeof(Tf);
-    if (cstep_lds_[0] <= kCStepLds) modes |= 1 << kCompactDense;
+    if (cstep_lds_[0] <= kCStepLds) *modes |= 1 << kCompactDense;
     // one workgroup: everything in LDS
     {
       uint32_t at = 0;
@@ -2042,69 +2077,74 @@ class EngineT final : public Engine {
       o.total = at;
       if (at <= kCSolveLds) {
         csolve_ = o;
-        modes |= 1 << kCompactBlock;
+        *modes |= 1 << kCompactBlock;
       }
     }
-    // global recursions: states of one step on chip, and a plant that does not amplify (FP64
-    // has the digits to spare: its limit is the growth that costs six of them)
+    return *modes ? compact_lists(cd_, rs, hs.nb_off, cdmem_, err) : DLMPC_OK;
+  }
+
+  // Global recursions: states of one step on chip, and a plant that does not amplify (FP64
+  // has the digits to spare: its limit is the growth that costs six of them).
+  int build_compact_global(int *modes, std::string &err) {
+    const HostSetup &hs = *hs_;
+    const int N = hs.N, NS = N * NX, nuT = hs.nu * (hs.T - 1), rs = hs.rs;
+    const int64_t R = int64_t(N) * rs;
     const double gmax = sizeof(Tf) == 8 ? 1e3 : 32.0;
-    if (nuT >= 1 && NS <= kCMaxStates && struct_ready_ && plant_growth(hs) <= gmax) {
-      CArgs<Tf> g = c;
-      g.glob = 1;
-      std::vector<std::vector<std::pair<int32_t, Tf>>> row(NS), col(NS);
-      for (int m = 0; m < N; ++m)
-        for (int64_t q = hs.a_rowptr[m]; q < hs.a_rowptr[m + 1]; ++q)
-          for (int e = 0; e < NX; ++e)
-            for (int f = 0; f < NX; ++f) {
-              const Tf v = static_cast<Tf>(hs.a_blocks[size_t(q) * NX * NX + e * NX + f]);
-              if (v == Tf(0)) continue;
-              row[e * N + m].push_back({f * N + hs.a_colidx[q], v});
-              col[f * N + hs.a_colidx[q]].push_back({e * N + m, v});
-            }
-      auto csr = [&](const std::vector<std::vector<std::pair<int32_t, Tf>>> &r, const int32_t **rp,
-                     const int32_t **ci, const Tf **va) {
-        std::vector<int32_t> p(1, 0), i;
-        std::vector<Tf> v;
-        for (const auto &x : r) {
-          for (const auto &e : x) {
-            i.push_back(e.first);
-            v.push_back(e.second);
+    int pm = 1;
+    for (int j = 0; j < N; ++j) pm = std::max(pm, int(hs.patch[j].size()));
+    cstep_lds_[1] = size_t((pm * nuT + 3) & ~3) * sizeof(Tf);
+    if (nuT < 1 || NS > kCMaxStates || !struct_ready_ || cstep_lds_[1] > kCStepLds || plant_growth(hs) > gmax)
+      return DLMPC_OK;
+    CArgs<Tf> &g = cg_;
+    int rc;
+    g.glob = 1;
+    std::vector<std::vector<std::pair<int32_t, Tf>>> row(NS), col(NS);
+    for (int m = 0; m < N; ++m)
+      for (int64_t q = hs.a_rowptr[m]; q < hs.a_rowptr[m + 1]; ++q)
+        for (int e = 0; e < NX; ++e)
+          for (int f = 0; f < NX; ++f) {
+            const Tf v = static_cast<Tf>(hs.a_blocks[size_t(q) * NX * NX + e * NX + f]);
+            if (v == Tf(0)) continue;
+            row[e * N + m].push_back({f * N + hs.a_colidx[q], v});
+            col[f * N + hs.a_colidx[q]].push_back({e * N + m, v});
           }
-          p.push_back(int32_t(i.size()));
+    auto csr = [&](const std::vector<std::vector<std::pair<int32_t, Tf>>> &r, const int32_t **rp,
+                   const int32_t **ci, const Tf **va) {
+      std::vector<int32_t> p(1, 0), i;
+      std::vector<Tf> v;
+      for (const auto &x : r) {
+        for (const auto &e : x) {
+          i.push_back(e.first);
+          v.push_back(e.second);
         }
-        int q;
-        if ((q = upload(p, rp, err)) || (q = upload(i, ci, err))) return q;
-        return upload(v, va, err);
-      };
-      std::vector<Tf> wt(R), lt(R), ut(R);
-      for (int m = 0; m < N; ++m)
-        for (int l = 0; l < rs; ++l) {
-          wt[size_t(l) * N + m] = static_cast<Tf>(hs.w[size_t(m) * rs + l]);
-          lt[size_t(l) * N + m] = static_cast<Tf>(hs.lb[size_t(m) * rs + l]);
-          ut[size_t(l) * N + m] = static_cast<Tf>(hs.ub[size_t(m) * rs + l]);
-        }
-      std::vector<int64_t> boff(N + 1, 0);
-      for (int j = 0; j < N; ++j)
-        boff[j + 1] = boff[j] + int64_t((int(hs.patch[j].size()) * nuT + 3) & ~3) * hs.kdim[j];
-      if ((rc = csr(row, &g.prp, &g.pcol, &g.pval)) || (rc = csr(col, &g.trp, &g.tcol, &g.tval)) ||
-          (rc = upload(wt, &g.w, err)) || (rc = upload(lt, &g.lb, err)) || (rc = upload(ut, &g.ub, err)) ||
-          (rc = alloc(&g.us, size_t(N) * nuT, err)) || (rc = alloc(&g.g, size_t(N) * nuT, err)) ||
-          (rc = alloc(&g.lam0, size_t(NS), err)) || (rc = lists(g, nuT, boff)))
-        return rc;
-      g.bblk = sa_.bblk;
-      g.basis = sa_.nbu;  // the structured Psi-comp's input rows, in the same layout
-      cg_ = g;
-      int pm = 1;
-      for (int j = 0; j < N; ++j) pm = std::max(pm, int(hs.patch[j].size()));
-      cstep_lds_[1] = size_t((pm * nuT + 3) & ~3) * sizeof(Tf);
-      if (cstep_lds_[1] <= kCStepLds) modes |= 1 << kCompactGlobal;
-    }
-    cmodes_ = modes;
+        p.push_back(int32_t(i.size()));
+      }
+      int q;
+      if ((q = upload(p, rp, err, cgmem_)) || (q = upload(i, ci, err, cgmem_))) return q;
+      return upload(v, va, err, cgmem_);
+    };
+    std::vector<Tf> wt(R), lt(R), ut(R);
+    for (int m = 0; m < N; ++m)
+      for (int l = 0; l < rs; ++l) {
+        wt[size_t(l) * N + m] = static_cast<Tf>(hs.w[size_t(m) * rs + l]);
+        lt[size_t(l) * N + m] = static_cast<Tf>(hs.lb[size_t(m) * rs + l]);
+        ut[size_t(l) * N + m] = static_cast<Tf>(hs.ub[size_t(m) * rs + l]);
+      }
+    std::vector<int64_t> boff(N + 1, 0);
+    for (int j = 0; j < N; ++j)
+      boff[j + 1] = boff[j] + int64_t((int(hs.patch[j].size()) * nuT + 3) & ~3) * hs.kdim[j];
+    if ((rc = csr(row, &g.prp, &g.pcol, &g.pval)) || (rc = csr(col, &g.trp, &g.tcol, &g.tval)) ||
+        (rc = upload(wt, &g.w, err, cgmem_)) || (rc = upload(lt, &g.lb, err, cgmem_)) || (rc = upload(ut, &g.ub, err, cgmem_)) ||
+        (rc = cgmem_.alloc(&g.us, size_t(N) * nuT, err)) || (rc = cgmem_.alloc(&g.g, size_t(N) * nuT, err)) ||
+        (rc = cgmem_.alloc(&g.lam0, size_t(NS), err)) || (rc = compact_lists(g, nuT, boff, cgmem_, err)))
+      return rc;
+    g.bblk = sa_.bblk;
+    g.basis = sa_.nbu;  // the structured Psi-comp's input rows, in the same layout
+    *modes |= 1 << kCompactGlobal;
     return DLMPC_OK;
   }
   static constexpr size_t kCSolveLds = 150 * 1024;
   static constexpr size_t kCStepLds = 44 * 1024;  // one patch's rows, beside the shares' 16 KB
-  int cmodes_ = -1;
   CArgs<Tf> cd_{}, cg_{};
   CSolveLds csolve_{};
   size_t cstep_lds_[2] = {0, 0};
@@ -2129,7 +2169,9 @@ class EngineT final : public Engine {
   PsiUnits<Tf> pu_{};
   int grid_ = 0;
   Sched sched_{};
-  std::vector<void *> owned_;
+  DeviceBuffers mem_;
+  DeviceBuffers smem_;                  // of the structured Psi-comp (the compact global form's bases too)
+  DeviceBuffers cmem_, cdmem_, cgmem_;  // of the compact form: shared, whole bases, global recursions
 };
 
 template <typename Tf>

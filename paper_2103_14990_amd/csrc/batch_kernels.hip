@@ -29,6 +29,7 @@
 #include <string>
 #include <vector>
 
+#include "device_buffers.h"
 #include "dlmpc_device.h"
 
 namespace dlmpc {
@@ -1743,7 +1744,7 @@ class BatchEngineT final : public BatchEngine {
       __bf16 *d_ntf = nullptr, *d_nf = nullptr;
       const int64_t *d_nboff = nullptr, *d_ntfoff = nullptr, *d_nfoff = nullptr, *d_toff = nullptr;
       const int32_t *d_k = nullptr;
-      if ((rc = al(&d_ntf, size_t(ntf_off[N]), err)) || (rc = al(&d_nf, size_t(nf_off[hs.n_tiles]), err)) ||
+      if ((rc = dmem_.alloc(&d_ntf, size_t(ntf_off[N]), err)) || (rc = dmem_.alloc(&d_nf, size_t(nf_off[hs.n_tiles]), err)) ||
           (rc = up(hs.nb_off, &d_nboff, err)) || (rc = up(ntf_off, &d_ntfoff, err)) ||
           (rc = up(nf_off, &d_nfoff, err)) || (rc = up(hs.tile_off, &d_toff, err)) || (rc = up(hs.kdim, &d_k, err)))
         return rc;
@@ -1792,7 +1793,7 @@ class BatchEngineT final : public BatchEngine {
           on2[size_t(j) * NX + c] += o * o;
         }
     }
-    if (!hs.d_nb && ((rc = up(ntf, &a.ntf, err)) || (rc = up(nf, &a.nf, err)))) return rc;
+    if (!hs.d_nb && ((rc = up(ntf, &a.ntf, err, dmem_)) || (rc = up(nf, &a.nf, err, dmem_)))) return rc;
     if ((rc = up(hs.tile_off, &a.tile_off, err)) || (rc = up(hs.rt_ptr, &a.rt_ptr, err)) ||
         (rc = up(hs.rt_tile, &a.rt_tile, err)) || (rc = up(hs.rt_col, &a.rt_col, err)) ||
         (rc = up(hs.kdim, &a.kdim, err)) || (rc = up(hs.tile_rsub, &a.tile_rsub, err)) ||
@@ -1815,8 +1816,8 @@ class BatchEngineT final : public BatchEngine {
     a.pj_n = d_pj_n;
     a.pj_first = d_pj_first;
     a.pj_off = d_pj_off;
-    if ((rc = al(&a.ppart, size_t(max_poff), err)) ||
-        (rc = al(&a.ppod, size_t(max_pfirst) * kBMax * 8 * NX, err)) || (rc = al(&a.pcnt, size_t(N), err)))
+    if ((rc = dmem_.alloc(&a.ppart, size_t(max_poff), err)) ||
+        (rc = dmem_.alloc(&a.ppod, size_t(max_pfirst) * kBMax * 8 * NX, err)) || (rc = al(&a.pcnt, size_t(N), err)))
       return rc;
     if ((rc = load_split(sp, kPsiCapDefault, err))) return rc;
     BENG_CHECK(hipMemset(a.pcnt, 0, sizeof(int32_t) * N));
@@ -1871,7 +1872,7 @@ class BatchEngineT final : public BatchEngine {
         const int64_t *d_nboff = nullptr, *d_ntuoff = nullptr, *d_toff = nullptr;
         const int32_t *d_k = nullptr;
         if (nnz_max <= kSNnz) {  // otherwise the patch dynamics exceed the kernel's staging
-          if ((rc = al(&d_ntu, size_t(std::max<int64_t>(ntu_off[N], 1)), err)) || (rc = up(hs.nb_off, &d_nboff, err)) ||
+          if ((rc = dmem_.alloc(&d_ntu, size_t(std::max<int64_t>(ntu_off[N], 1)), err)) || (rc = up(hs.nb_off, &d_nboff, err)) ||
               (rc = up(ntu_off, &d_ntuoff, err)) || (rc = up(hs.tile_off, &d_toff, err)) || (rc = up(hs.kdim, &d_k, err)) ||
               (rc = up(srp0, &a.srp0, err)) || (rc = up(se0, &a.se0, err)) || (rc = up(srpt, &a.srpt, err)) ||
               (rc = up(scolt, &a.scolt, err)) || (rc = up(svalt, &a.svalt, err)))
@@ -1895,7 +1896,7 @@ class BatchEngineT final : public BatchEngine {
     const size_t ny = size_t(N) * hs.rs;
     if ((rc = al(&a.alpha, 2 * size_t(bmax) * ny, err)) || (rc = al(&a.tau, size_t(bmax) * a.ktot, err)) ||
         (rc = al(&a.eta, 2 * size_t(bmax) * a.ktot, err)) || (rc = al(&a.xn, size_t(bmax) * N, err)) ||
-        (rc = al(&a.nrm, size_t(bmax) * N, err)) || (rc = al(&a.bvec, size_t(bmax) * ny, err)) ||
+        (rc = al(&a.nrm, size_t(bmax) * N, err)) || (rc = dmem_.alloc(&a.bvec, size_t(bmax) * ny, err)) ||
         (rc = al(&a.s, size_t(bmax) * ny, err)) || (rc = al(&a.x0, size_t(bmax) * N * NX, err)) ||
         (rc = al(&a.ictl, size_t(bmax), err)) || (rc = al(&a.slot, 2 * size_t(bmax), err)) ||
         (rc = al(&a.ctl, 1, err)) || (rc = al(&d_slots_, size_t(bmax), err)) ||
@@ -1917,8 +1918,8 @@ class BatchEngineT final : public BatchEngine {
 
     // trajectory warm start: vectors and the plant in FP32
     a.Bw = (bmax + 15) & ~15;
-    if ((rc = al(&a.w_hi, size_t(a.Bw) * a.ktot, err)) || (rc = al(&a.w_lo, size_t(a.Bw) * a.ktot, err)) ||
-        (rc = al(&a.dlm, size_t(bmax) * N, err)))
+    if ((rc = dmem_.alloc(&a.w_hi, size_t(a.Bw) * a.ktot, err)) ||
+        (rc = dmem_.alloc(&a.w_lo, size_t(a.Bw) * a.ktot, err)) || (rc = al(&a.dlm, size_t(bmax) * N, err)))
       return rc;
     // padded k entries and instances of W stay zero: the products read whole 32-wide k blocks
     // of 16 instances
@@ -1963,12 +1964,6 @@ class BatchEngineT final : public BatchEngine {
     a.rb = 1;
     a.rm = int64_t(hs.rs) * bmax;
     a.rl = bmax;
-    if ((rc = init_global(err)) == DLMPC_ENOMEM) {  // no memory for it: the dense products
-      (void)hipGetLastError();
-      err.clear();
-    } else if (rc) {
-      return rc;
-    }
     a.phi_mode = 0;
     a.src = nullptr;
     a.dst_k = nullptr;
@@ -2240,11 +2235,36 @@ class BatchEngineT final : public BatchEngine {
     *n_units = n_units_;
   }
 
+  int build_global(std::string &err) override {
+    const BArgs keep = args_;
+    const int rc = build_optional(gmem_, [&] { return init_global(err); }, &glob_ok_, err);
+    glob_ok_ = glob_ok_ && args_.ngu;
+    if (!glob_ok_) args_ = keep;
+    return rc;
+  }
+  void settle() override {
+    BArgs &a = args_;
+    if (glob_) {
+      dmem_.give_back();
+      a.ntf = a.nf = a.ntu = a.w_hi = a.w_lo = nullptr;
+      a.ppart = a.bvec = nullptr;
+      a.ppod = nullptr;
+      dense_ok_ = struct_ok_ = false;
+    } else {
+      gmem_.give_back();
+      a.ngu = a.ngv = nullptr;
+      glob_ok_ = false;
+    }
+  }
   bool global_available() const override { return glob_ok_; }
   bool global_on() const override { return glob_; }
   int set_global(bool on, std::string &err) override {
     if (on && !glob_ok_) {
       err = "the iteration through the global recursions is not available for this problem";
+      return DLMPC_EINVAL;
+    }
+    if (!on && !dense_ok_) {
+      err = "the dense products' buffers were given back";
       return DLMPC_EINVAL;
     }
     BENG_CHECK(hipStreamSynchronize(stream_));
@@ -2325,28 +2345,20 @@ class BatchEngineT final : public BatchEngine {
   BCtl *ictl() override { return args_.ictl; }
   int bmax() const override { return args_.Bmax; }
 
-  ~BatchEngineT() override {
-    for (void *p : owned_) (void)hipFree(p);
-  }
-
  private:
   template <typename U>
   int al(U **dst, size_t n, std::string &err) {
-    void *p = nullptr;
-    const size_t bytes = std::max<size_t>(n, 1) * sizeof(U);
-    if (hipMalloc(&p, bytes) != hipSuccess) {
-      err = "hipMalloc of " + std::to_string(bytes) + " bytes failed";
-      return DLMPC_ENOMEM;
-    }
-    owned_.push_back(p);
-    *dst = static_cast<U *>(p);
-    return DLMPC_OK;
+    return mem_.alloc(dst, n, err);
   }
   template <typename U, typename V>
   int up(const std::vector<U> &src, V **dst, std::string &err) {
+    return up(src, dst, err, mem_);
+  }
+  template <typename U, typename V>
+  int up(const std::vector<U> &src, V **dst, std::string &err, DeviceBuffers &mem) {
     static_assert(sizeof(U) == sizeof(V), "upload type");
     U *p = nullptr;
-    int rc = al(&p, src.size(), err);
+    int rc = mem.alloc(&p, src.size(), err);
     if (rc) return rc;
     if (!src.empty()) BENG_CHECK(hipMemcpy(p, src.data(), src.size() * sizeof(U), hipMemcpyHostToDevice));
     *dst = reinterpret_cast<V *>(p);
@@ -2429,7 +2441,6 @@ class BatchEngineT final : public BatchEngine {
     const HostSetup &hs = *hs_;
     BArgs &a = args_;
     const int N = hs.N, NS = N * NX, nuT = hs.nu * (hs.T - 1);
-    glob_ok_ = false;
     if (!split_ || nuT < 1 || NS > kSimStates) return DLMPC_OK;
     sim_lds_ = (size_t(2) * kSimStates + size_t(N) * nuT) * sizeof(float);
     sim_start_lds_ = (size_t(4) * kSimStates + size_t(N) * nuT) * sizeof(float);
@@ -2471,8 +2482,8 @@ class BatchEngineT final : public BatchEngine {
         p.push_back(int32_t(i.size()));
       }
       int q;
-      if ((q = up(p, rp, err)) || (q = up(i, ci, err))) return q;
-      return up(v, va, err);
+      if ((q = up(p, rp, err, gmem_)) || (q = up(i, ci, err, gmem_))) return q;
+      return up(v, va, err, gmem_);
     };
     if ((rc = csr(row, &a.prp, &a.pcol, &a.pval)) || (rc = csr(col, &a.trp, &a.tcol, &a.tval))) return rc;
     std::vector<float> wt(ny_), lt(ny_), ut(ny_);
@@ -2482,7 +2493,7 @@ class BatchEngineT final : public BatchEngine {
         lt[size_t(l) * N + m] = float(hs.lb[size_t(m) * hs.rs + l]);
         ut[size_t(l) * N + m] = float(hs.ub[size_t(m) * hs.rs + l]);
       }
-    if ((rc = up(wt, &a.wT, err)) || (rc = up(lt, &a.lbT, err)) || (rc = up(ut, &a.ubT, err))) return rc;
+    if ((rc = up(wt, &a.wT, err, gmem_)) || (rc = up(lt, &a.lbT, err, gmem_)) || (rc = up(ut, &a.ubT, err, gmem_))) return rc;
     std::vector<int64_t> uo(N + 1, 0), vo(N + 1, 0);
     for (int j = 0; j < N; ++j) {
       const int64_t mu = int64_t(hs.patch[j].size()) * nuT, k = hs.kdim[j];
@@ -2506,11 +2517,11 @@ class BatchEngineT final : public BatchEngine {
     }
     __bf16 *fu = nullptr, *fv = nullptr;
     const size_t bm = size_t(a.Bmax);
-    if ((rc = up(uo, &a.ngu_off, err)) || (rc = up(sd, &a.sdesc, err)) || (rc = up(vo, &a.ngv_off, err)) || (rc = al(&fu, size_t(uo[N]), err)) ||
-        (rc = al(&fv, size_t(vo[N]), err)) || (rc = al(&a.bu, bm * N * nuT, err)) ||
-        (rc = al(&a.usum, bm * N * nuT, err)) || (rc = al(&a.gu, bm * N * nuT, err)) ||
-        (rc = al(&a.upart, size_t(hs.n_tiles) * nuT * a.Bw, err)) || (rc = al(&a.lam0, bm * NS, err)) ||
-        (rc = al(&a.rres, bm * 2 * N, err)) || (rc = al(&a.dlq, bm * kSimParts * N, err)))
+    if ((rc = up(uo, &a.ngu_off, err, gmem_)) || (rc = up(sd, &a.sdesc, err, gmem_)) || (rc = up(vo, &a.ngv_off, err, gmem_)) || (rc = gmem_.alloc(&fu, size_t(uo[N]), err)) ||
+        (rc = gmem_.alloc(&fv, size_t(vo[N]), err)) || (rc = gmem_.alloc(&a.bu, bm * N * nuT, err)) ||
+        (rc = gmem_.alloc(&a.usum, bm * N * nuT, err)) || (rc = gmem_.alloc(&a.gu, bm * N * nuT, err)) ||
+        (rc = gmem_.alloc(&a.upart, size_t(hs.n_tiles) * nuT * a.Bw, err)) || (rc = gmem_.alloc(&a.lam0, bm * NS, err)) ||
+        (rc = gmem_.alloc(&a.rres, bm * 2 * N, err)) || (rc = gmem_.alloc(&a.dlq, bm * kSimParts * N, err)))
       return rc;
     BENG_CHECK(hipMemset(fu, 0, sizeof(__bf16) * std::max<int64_t>(uo[N], 1)));
     BENG_CHECK(hipMemset(fv, 0, sizeof(__bf16) * std::max<int64_t>(vo[N], 1)));
@@ -2520,7 +2531,6 @@ class BatchEngineT final : public BatchEngine {
     BENG_CHECK(hipDeviceSynchronize());
     a.ngu = fu;
     a.ngv = fv;
-    glob_ok_ = true;
     return DLMPC_OK;
   }
   dim3 sim_threads() const { return dim3(std::min(kSimThreads, (hs_->N * NX + 63) & ~63)); }
@@ -2588,7 +2598,7 @@ class BatchEngineT final : public BatchEngine {
     const size_t lds = size_t(args_.Bw) * ((hs_->nu * (hs_->T - 1)) | 1) * sizeof(float);
     hipLaunchKernelGGL(bgather_kernel, dim3(hs_->N + args_.Bmax), dim3(256), lds, stream_, x);
   }
-  bool glob_ok_ = false, glob_ = false, sim_both_ = false;
+  bool glob_ok_ = false, glob_ = false, dense_ok_ = true, sim_both_ = false;
   int step_nt_ = 1, step_mt_ = 1, step_wn_ = 1;
   size_t sim_lds_ = 0, sim_start_lds_ = 0, step_lds_ = 0;
   int nrt_ = 1, mtw_ = 1;
@@ -2621,7 +2631,9 @@ class BatchEngineT final : public BatchEngine {
     return sa;
   }
   int n_units_ = 0;  // Psi-comp work units
-  std::vector<void *> owned_;
+  DeviceBuffers mem_;
+  DeviceBuffers dmem_;  // of the dense products only
+  DeviceBuffers gmem_;  // of the global recursions only
 };
 
 // flag[0] = 1 if some entry of x[0..n) is NaN or +-Inf (flag cleared by the caller).

@@ -358,6 +358,7 @@ int tune_batch(dlmpc_problem *p) {
     for (int c = 0; c < 6; ++c)
       if (p->tune_psi_us[c] > 0.0 && p->tune_psi_us[c] < 0.99 * p->tune_psi_us[best_c]) best_c = c;
     if ((rc = p->beng->set_variant(ntw, caps[best_c], err))) return fail(rc, err);
+    if ((rc = p->beng->build_global(err))) return fail(rc, err);
     if (!p->beng->global_available()) return DLMPC_OK;
     double dense = p->tune_phi_us[ntw - 1] + p->tune_psi_us[best_c], t = 0.0, sum = 0.0;
     if ((rc = time_k(2, &t))) return rc;
@@ -412,18 +413,21 @@ int setup_batch(dlmpc_problem *p) {
   if (p->opt.flags & DLMPC_FLAG_NO_TUNE) {
     // untimed: the global recursions wherever the problem allows them (faster from the 8 x 8 grid
     // to the 1024-node mesh)
+    if ((rc = p->beng->build_global(err))) return fail(rc, err);
     if (p->beng->global_available() && (rc = p->beng->set_global(true, err))) return fail(rc, err);
   } else {
     int ntw = 0, capx = 0, sched = 0, glob = 0, comp = 0;
     std::string err2;
     if (tune_cache_read(tune_signature(p), &ntw, &capx, &sched, &glob, &comp) && !p->beng->set_variant(ntw, capx, err2)) {
       p->tune_cached = 1;
+      if (glob && (rc = p->beng->build_global(err))) return fail(rc, err);
       if (glob && p->beng->global_available() && (rc = p->beng->set_global(true, err))) return fail(rc, err);
     } else {
       rc = tune_batch(p);
       if (rc) return rc;
     }
   }
+  p->beng->settle();
   for (int joins = 0; joins < 2; ++joins)
     for (int g = 0; g < dlmpc_problem::kGraphs; ++g) {
       API_HIP(hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
@@ -595,15 +599,20 @@ int choose_schedule(dlmpc_problem *p) {
     return capture_single(p);
   };
   std::string err;
-  const int modes = p->eng->compact_modes(err);
-  if (modes < 0) return fail(modes, err);
-  if (tune_cache_read(sig, &ntw, &capx, &sched, &glob, &comp) && (comp == 0 || (modes >> comp & 1)) && (sched == 0 || (sched == 1 && can_persist) ||
-                                                    (sched == 2 && p->struct_ok))) {
-    p->tune_cached = 1;
-    p->compact = comp;
-    if ((comp == dlmpc::kCompactDense || comp == dlmpc::kCompactGlobal) && (rc = capture_compact(p, comp))) return rc;
-    return apply(sched);
+  if (tune_cache_read(sig, &ntw, &capx, &sched, &glob, &comp) &&
+      (sched == 0 || (sched == 1 && can_persist) || (sched == 2 && p->struct_ok))) {
+    const int got = comp ? p->eng->compact_modes(1 << comp, err) : 0;
+    if (got < 0) return fail(got, err);
+    if (comp == 0 || (got >> comp & 1)) {
+      p->tune_cached = 1;
+      p->compact = comp;
+      p->eng->settle(comp, sched == 2);
+      if ((comp == dlmpc::kCompactDense || comp == dlmpc::kCompactGlobal) && (rc = capture_compact(p, comp))) return rc;
+      return apply(sched);
+    }
   }
+  const int modes = p->eng->compact_modes(1 << dlmpc::kCompactDense | 1 << dlmpc::kCompactGlobal | 1 << dlmpc::kCompactBlock, err);
+  if (modes < 0) return fail(modes, err);
   const int n = 32;
   if ((rc = time_schedule(p, 0, n, &p->tune_graph_us))) return rc;
   if (can_persist) {
@@ -639,6 +648,7 @@ int choose_schedule(dlmpc_problem *p) {
       p->compact = m;
     }
   }
+  p->eng->settle(p->compact, best == 2);
   if ((p->compact == dlmpc::kCompactDense || p->compact == dlmpc::kCompactGlobal) &&
       (rc = capture_compact(p, p->compact)))
     return rc;

@@ -161,11 +161,14 @@ class Engine {
   virtual Ctl *ctl() = 0;
   // Compact form of the iteration from the cold start (single_compact.h): which of kCompactDense
   // (products with whole bases), kCompactGlobal (input rows and the plant's global recursions) and
-  // kCompactBlock (a whole solve in one workgroup) this problem allows, as a bit mask (1 << mode;
-  // negative: a status; builds their buffers on the first call); the per-solve set-up, one iteration (capturable), the
-  // decision that closes a chunk of iterations, a whole solve (kCompactBlock), and the expansion of
-  // the stopping iterate into Phi, Psi, Lambda and y.
-  virtual int compact_modes(std::string &err) = 0;
+  // kCompactBlock (a whole solve in one workgroup) of the bit mask `want` (1 << mode) this problem and
+  // the memory left allow, as a bit mask (negative: a status; builds their buffers); the per-solve
+  // set-up, one iteration (capturable), the decision that closes a chunk of iterations, a whole
+  // solve (kCompactBlock), and the expansion of the stopping iterate into Phi, Psi, Lambda and y.
+  // settle gives back, for good, the buffers of the compact forms other than `mode` (0: all) and
+  // those of the structured Psi-comp where neither that mode nor the standard form needs them.
+  virtual int compact_modes(int want, std::string &err) = 0;
+  virtual void settle(int mode, bool structured) = 0;
   virtual int compact_precompute(int mode, const double *x0_dev, int max_iter, double eps, double rho,
                                  std::string &err) = 0;
   virtual int compact_iteration(int mode, std::string &err) = 0;
@@ -329,9 +332,13 @@ class BatchEngine {
   // mean; one of 2, 4, 8, 16, 1 << 20). Synchronises the engine's stream.
   virtual int set_variant(int phi_ntw, int psi_capx, std::string &err) = 0;
   virtual void variant(int *phi_ntw, int *psi_capx, int *n_units) const = 0;
-  // Iteration through the plant's global recursions (split operands; batch_global.h): whether this
-  // problem allows it, and the switch between it and the dense products (before graph capture;
-  // the next solve must start with precompute). Synchronises the engine's stream.
+  // Iteration through the plant's global recursions (split operands; batch_global.h): builds it where
+  // the problem and the memory left allow it (after the allocations that setup cannot do without),
+  // whether it is there, and the switch between it and the dense products (before graph capture;
+  // the next solve must start with precompute; synchronises the engine's stream). settle gives
+  // back the buffers of the form that is not on, for good.
+  virtual int build_global(std::string &err) = 0;
+  virtual void settle() = 0;
   virtual bool global_available() const = 0;
   virtual int set_global(bool on, std::string &err) = 0;
   virtual bool global_on() const = 0;
