@@ -228,8 +228,8 @@ typedef struct {
   int32_t factor_device; /* 1 if the column blocks were factored on the device, 0 on the host */
   int32_t factor_fallbacks; /* device factorisation: subsystems whose null basis came from the
                                Householder QR because Cholesky QR of S K met a tiny pivot */
-  /* Autotuner (dlmpc_setup). The single-instance schedule (graph or persistent, each timed over 32
-   * iterations in the standard form, all of Phi, Psi and Lambda in every iteration, and in the
+  /* Autotuner (dlmpc_setup). The single-instance schedule (graph or persistent, each timed over a
+   * few iterations in the standard form, all of Phi, Psi and Lambda in every iteration, and in the
    * compact form of the cold start, row multipliers and null-space coordinates with Phi, Psi and
    * Lambda written after the stop; the times reported are those of the faster form; given starts and
    * couplings always run the standard form) and the batched engine's kernel variants are chosen by timing at setup, or taken

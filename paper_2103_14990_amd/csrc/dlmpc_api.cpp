@@ -147,11 +147,11 @@ void release_device(dlmpc_problem *p) {
 
 int choose_schedule(dlmpc_problem *p);
 
-// (Re)captures the single-instance iteration graphs of 2^g iterations (synchronises).
-int capture_single(dlmpc_problem *p) {
+// (Re)captures the single-instance iteration graphs of 2^g iterations, first <= g < last (synchronises).
+int capture_single(dlmpc_problem *p, int first = 0, int last = dlmpc_problem::kGraphs) {
   std::string err;
   API_HIP(hipStreamSynchronize(p->stream));
-  for (int g = 0; g < dlmpc_problem::kGraphs; ++g) {
+  for (int g = first; g < last; ++g) {
     if (p->gexec[g]) (void)hipGraphExecDestroy(p->gexec[g]);
     if (p->graph[g]) (void)hipGraphDestroy(p->graph[g]);
     p->gexec[g] = nullptr;
@@ -173,12 +173,12 @@ int capture_single(dlmpc_problem *p) {
   return DLMPC_OK;
 }
 
-// (Re)captures the compact iteration's graphs of 2^g iterations (g >= first), each closed by its
-// decision.
-int capture_compact(dlmpc_problem *p, int mode, int first = 0) {
+// (Re)captures the compact iteration's graphs of 2^g iterations (first <= g < last), each closed by
+// its decision.
+int capture_compact(dlmpc_problem *p, int mode, int first = 0, int last = dlmpc_problem::kGraphs) {
   std::string err;
   API_HIP(hipStreamSynchronize(p->stream));
-  for (int g = first; g < dlmpc_problem::kGraphs; ++g) {
+  for (int g = first; g < last; ++g) {
     if (p->cgexec[g]) (void)hipGraphExecDestroy(p->cgexec[g]);
     if (p->cgraph[g]) (void)hipGraphDestroy(p->cgraph[g]);
     p->cgexec[g] = nullptr;
@@ -243,9 +243,9 @@ int setup_device(dlmpc_problem *p) {
   for (auto *e : {&p->ev_p0, &p->ev_p1, &p->ev_c0, &p->ev_c1}) API_HIP(hipEventCreate(e));
   API_HIP(hipMalloc(&p->d_flag, sizeof(int32_t)));
   API_HIP(hipHostMalloc(reinterpret_cast<void **>(&p->h_flag), sizeof(int32_t), hipHostMallocDefault));
-  // Iteration graphs of 2^g iterations; every launch after the device-side stop is a no-op.
+  // Iteration graphs of 2^g iterations (choose_schedule captures them); every launch after the
+  // device-side stop is a no-op.
   p->K = p->opt.check_every > 0 ? std::min(p->opt.check_every, p->opt.max_iter) : 32;
-  if ((rc = capture_single(p))) return rc;
   if (p->opt.max_batch > 0) {
     rc = setup_batch(p);
     if (rc) return rc;
@@ -496,63 +496,80 @@ struct ChunkPredictor {
   }
 };
 
-// Times n iterations of a schedule from x0 = (1, ..., 1) with the stop test disabled.
-int time_schedule(dlmpc_problem *p, int sched, int n, double *us_per_iter) {
-  std::string err;
+// Iterations that setup times a form over: graphs of 2^g iterations, one of them to warm code and
+// caches and one timed; the forms of one launch over 2^(g+1), after a few. 16 iterations of the
+// smallest networks take 70 us and more; where the bases have 256 MB an iteration takes 80 us and
+// more, and four tell the forms apart. (Twice 32 iterations each, as before: 121 of the 217 ms that
+// setup took on the 1024-node mesh in FP64.)
+int timed_graph(const dlmpc_problem *p) {
+  const double bytes = double(p->hs.sum_dcol_k) * (p->opt.precision == DLMPC_FP64 ? 8 : 4);
+  return bytes >= 256e6 ? 2 : 4;
+}
+
+// Times a form of the single solve (run enqueues n iterations after start) from x0 = (1, ..., 1) with
+// the stop test disabled.
+template <class Start, class Run>
+int time_form(dlmpc_problem *p, int warm, int n, Start start, Run run, double *us_per_iter) {
   const HostSetup &hs = p->hs;
   std::vector<double> ones(size_t(hs.N) * hs.nx, 1.0);
   API_HIP(hipMemcpy(p->d_x0, ones.data(), ones.size() * sizeof(double), hipMemcpyHostToDevice));
-  float best = 1e30f;
-  for (int rep = 0; rep < 2; ++rep) {  // the first repetition warms code and caches
-    int rc = p->eng->precompute(p->d_x0, nullptr, nullptr, n, -1.0, p->opt.rho, err);
-    if (rc) return fail(rc, err);
+  for (int k : {warm, n}) {
+    int rc = start(k);
+    if (rc) return rc;
     API_HIP(hipEventRecord(p->ev_t0, p->stream));
-    if (sched == 1) {
-      rc = p->eng->run_persistent(true, err);
-      if (rc) return fail(rc, err);
-    } else {
-      rc = launch_iterations(p, n);
-      if (rc) return rc;
-    }
+    if ((rc = run(k))) return rc;
     API_HIP(hipEventRecord(p->ev_t1, p->stream));
     API_HIP(hipStreamSynchronize(p->stream));
-    float ms = 0.f;
-    API_HIP(hipEventElapsedTime(&ms, p->ev_t0, p->ev_t1));
-    best = std::min(best, ms);
-    API_HIP(hipMemcpy(&p->h_ctl[0], p->eng->ctl(), sizeof(Ctl), hipMemcpyDeviceToHost));
-    if (p->h_ctl[0].bar_fail) return fail(DLMPC_EDEVICE, "persistent grid barrier timed out");
   }
-  *us_per_iter = 1e3 * double(best) / n;
+  float ms = 0.f;
+  API_HIP(hipEventElapsedTime(&ms, p->ev_t0, p->ev_t1));
+  *us_per_iter = 1e3 * double(ms) / n;
   return DLMPC_OK;
 }
 
-// The same for the compact form.
-int time_compact(dlmpc_problem *p, int mode, int n, double *us_per_iter) {
+// A schedule of the standard form: 0 graph (captures the graph that it times), 1 persistent.
+int time_schedule(dlmpc_problem *p, int sched, double *us_per_iter) {
   std::string err;
-  const HostSetup &hs = p->hs;
-  std::vector<double> ones(size_t(hs.N) * hs.nx, 1.0);
-  API_HIP(hipMemcpy(p->d_x0, ones.data(), ones.size() * sizeof(double), hipMemcpyHostToDevice));
-  int g = 0;  // n is a power of two that has a graph
-  while ((2 << g) <= n && g + 1 < dlmpc_problem::kGraphs) ++g;
-  int rc = mode == dlmpc::kCompactBlock ? DLMPC_OK : capture_compact(p, mode, g);
+  const int g = timed_graph(p), n = sched == 1 ? 2 << g : 1 << g;
+  int rc = sched == 1 ? DLMPC_OK : capture_single(p, g, g + 1);
   if (rc) return rc;
-  float best = 1e30f;
-  for (int rep = 0; rep < 2; ++rep) {
-    if ((rc = p->eng->compact_precompute(mode, p->d_x0, n, -1.0, p->opt.rho, err))) return fail(rc, err);
-    API_HIP(hipEventRecord(p->ev_t0, p->stream));
-    if (mode == dlmpc::kCompactBlock) {
-      if ((rc = p->eng->compact_solve(err))) return fail(rc, err);
-    } else if ((rc = launch_graphs(p->cgexec, p->stream, n))) {
-      return rc;
-    }
-    API_HIP(hipEventRecord(p->ev_t1, p->stream));
-    API_HIP(hipStreamSynchronize(p->stream));
-    float ms = 0.f;
-    API_HIP(hipEventElapsedTime(&ms, p->ev_t0, p->ev_t1));
-    best = std::min(best, ms);
-  }
-  *us_per_iter = 1e3 * double(best) / n;
+  rc = time_form(
+      p, sched == 1 ? n / 8 : n, n,
+      [&](int k) {
+        const int r = p->eng->precompute(p->d_x0, nullptr, nullptr, k, -1.0, p->opt.rho, err);
+        return r ? fail(r, err) : DLMPC_OK;
+      },
+      [&](int k) -> int {
+        if (sched != 1) return launch_iterations(p, k);
+        const int r = p->eng->run_persistent(true, err);
+        return r ? fail(r, err) : DLMPC_OK;
+      },
+      us_per_iter);
+  if (rc) return rc;
+  API_HIP(hipMemcpy(&p->h_ctl[0], p->eng->ctl(), sizeof(Ctl), hipMemcpyDeviceToHost));
+  if (p->h_ctl[0].bar_fail) return fail(DLMPC_EDEVICE, "persistent grid barrier timed out");
   return DLMPC_OK;
+}
+
+// The same for a compact form.
+int time_compact(dlmpc_problem *p, int mode, double *us_per_iter) {
+  std::string err;
+  const bool one = mode == dlmpc::kCompactBlock;
+  const int g = timed_graph(p), n = one ? 2 << g : 1 << g;
+  const int rc = one ? DLMPC_OK : capture_compact(p, mode, g, g + 1);
+  if (rc) return rc;
+  return time_form(
+      p, one ? n / 8 : n, n,
+      [&](int k) {
+        const int r = p->eng->compact_precompute(mode, p->d_x0, k, -1.0, p->opt.rho, err);
+        return r ? fail(r, err) : DLMPC_OK;
+      },
+      [&](int k) -> int {
+        if (!one) return launch_graphs(p->cgexec, p->stream, k);
+        const int r = p->eng->compact_solve(err);
+        return r ? fail(r, err) : DLMPC_OK;
+      },
+      us_per_iter);
 }
 
 int choose_schedule(dlmpc_problem *p) {
@@ -567,25 +584,25 @@ int choose_schedule(dlmpc_problem *p) {
     p->sched = per_iter;
     if (per_iter >= 4)
       API_HIP(hipHostMalloc(&p->h_xchg, p->eng->exchange_bytes(), hipHostMallocDefault));
-    return DLMPC_OK;
+    return capture_single(p);
   }
   if (f & DLMPC_FLAG_SCHED_GRAPH) {
     p->sched = 0;
-    return DLMPC_OK;
+    return capture_single(p);
   }
   if (f & DLMPC_FLAG_STRUCTURED_PSI) {  // the persistent kernel runs the dense Psi-comp only
     if (f & DLMPC_FLAG_SCHED_PERSISTENT) return fail(DLMPC_EINVAL, "the structured Psi-comp runs on the graph schedule");
     p->sched = 0;
-    return DLMPC_OK;
+    return capture_single(p);
   }
   if (f & DLMPC_FLAG_SCHED_PERSISTENT) {
     if (!can_persist) return fail(DLMPC_EDEVICE, "persistent schedule unavailable on this device");
     p->sched = 1;
-    return DLMPC_OK;
+    return capture_single(p);
   }
   if (f & DLMPC_FLAG_NO_TUNE) {
     p->sched = 0;
-    return DLMPC_OK;
+    return capture_single(p);
   }
   const std::string sig = tune_signature(p);
   int rc = DLMPC_OK;
@@ -613,16 +630,11 @@ int choose_schedule(dlmpc_problem *p) {
   }
   const int modes = p->eng->compact_modes(1 << dlmpc::kCompactDense | 1 << dlmpc::kCompactGlobal | 1 << dlmpc::kCompactBlock, err);
   if (modes < 0) return fail(modes, err);
-  const int n = 32;
-  if ((rc = time_schedule(p, 0, n, &p->tune_graph_us))) return rc;
-  if (can_persist) {
-    rc = time_schedule(p, 1, n, &p->tune_persistent_us);
-    if (rc) return rc;
-  }
+  if ((rc = time_schedule(p, 0, &p->tune_graph_us))) return rc;
+  if (can_persist && (rc = time_schedule(p, 1, &p->tune_persistent_us))) return rc;
   if (p->struct_ok) {
-    if ((rc = apply(2))) return rc;
-    rc = time_schedule(p, 0, n, &p->tune_structured_us);
-    if (rc) return rc;
+    p->eng->set_structured(true);
+    if ((rc = time_schedule(p, 0, &p->tune_structured_us))) return rc;
   }
   int best = 0;
   double best_us = p->tune_graph_us;
@@ -641,7 +653,7 @@ int choose_schedule(dlmpc_problem *p) {
   for (int m : {dlmpc::kCompactDense, dlmpc::kCompactGlobal, dlmpc::kCompactBlock}) {
     if (!(modes >> m & 1)) continue;
     double t = 0.0;
-    if ((rc = time_compact(p, m, n, &t))) return rc;
+    if ((rc = time_compact(p, m, &t))) return rc;
     if (*tune[m] <= 0.0 || t < *tune[m]) *tune[m] = t;
     if (t < best_us) {
       best_us = t;

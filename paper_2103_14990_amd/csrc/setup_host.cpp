@@ -688,27 +688,34 @@ void factor_lists(const HostSetup &hs, FactorLists &fl) {
 }
 
 double plant_growth(const HostSetup &hs) {
+  constexpr int V = 8;  // the vectors side by side: [state][V]
   const int N = hs.N, nx = hs.nx;
-  double g = 0.0;
-  for (int v = 0; v < 8; ++v) {
-    std::vector<double> x(size_t(N) * nx), y(size_t(N) * nx);
+  std::vector<double> x(size_t(N) * nx * V), y(x.size());
+  for (int v = 0; v < V; ++v) {
     uint64_t h = 0x9e3779b97f4a7c15ull * uint64_t(v + 1);
-    for (auto &e : x) {
+    for (size_t e = 0; e < size_t(N) * nx; ++e) {
       h = h * 6364136223846793005ull + 1442695040888963407ull;
-      e = (h >> 63) ? 1.0 : -1.0;
+      x[e * V + v] = (h >> 63) ? 1.0 : -1.0;
     }
-    for (int t = 1; t < hs.T; ++t) {
-      for (int m = 0; m < N; ++m)
-        for (int c = 0; c < nx; ++c) {
-          double s = 0.0;
-          for (int64_t q = hs.a_rowptr[m]; q < hs.a_rowptr[m + 1]; ++q)
-            for (int c2 = 0; c2 < nx; ++c2)
-              s += hs.a_blocks[size_t(q) * nx * nx + c * nx + c2] * x[size_t(hs.a_colidx[q]) * nx + c2];
-          y[size_t(m) * nx + c] = s;
-          g = std::max(g, std::fabs(s));
+  }
+  double g = 0.0;
+  for (int t = 1; t < hs.T; ++t) {
+    for (int m = 0; m < N; ++m)
+      for (int c = 0; c < nx; ++c) {
+        double s[V] = {};
+        for (int64_t q = hs.a_rowptr[m]; q < hs.a_rowptr[m + 1]; ++q)
+          for (int c2 = 0; c2 < nx; ++c2) {
+            const double a = hs.a_blocks[size_t(q) * nx * nx + c * nx + c2];
+            const double *xv = &x[(size_t(hs.a_colidx[q]) * nx + c2) * V];
+            for (int v = 0; v < V; ++v) s[v] += a * xv[v];
+          }
+        double *yv = &y[(size_t(m) * nx + c) * V];
+        for (int v = 0; v < V; ++v) {
+          yv[v] = s[v];
+          g = std::max(g, std::fabs(s[v]));
         }
-      x.swap(y);
-    }
+      }
+    x.swap(y);
   }
   return g;
 }
