@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "dlmpc_device.h"
+#include "tune_rule.h"
 
 using dlmpc::Ctl;
 using dlmpc::HostSetup;
@@ -308,7 +309,7 @@ void tune_cache_write(const std::string &sig, int phi_ntw, int psi_capx, int sch
 // Times the batched-engine variants with max_batch instances from a zero-multiplier start (every
 // launch does the full work; x0 = 1 everywhere) and keeps the fastest Phi-comp and Psi-comp; then
 // the iteration through the global recursions, kept when its launches take less time than those
-// of the chosen dense variants.
+// of the chosen dense variants (dlmpc::replaces).
 int tune_batch(dlmpc_problem *p) {
   const HostSetup &hs = p->hs;
   const int B = p->beng->bmax();
@@ -345,8 +346,7 @@ int tune_batch(dlmpc_problem *p) {
       if ((rc = p->beng->set_variant(v + 1, cur_cap, err))) return fail(rc, err);
       if ((rc = time_k(0, &p->tune_phi_us[v]))) return rc;
     }
-    // a candidate replaces the default only when it is faster by more than timing noise (1 %)
-    const int ntw = p->tune_phi_us[1] < 0.99 * p->tune_phi_us[0] ? 2 : 1;
+    const int ntw = dlmpc::replaces(p->tune_phi_us[1], p->tune_phi_us[0]) ? 2 : 1;
     // splits of heavy column blocks, and the structured Psi-comp (0) where the problem allows it
     static const int caps[6] = {2, 4, 8, 16, 1 << 20, 0};
     for (int c = 0; c < 6; ++c) {
@@ -356,7 +356,7 @@ int tune_batch(dlmpc_problem *p) {
     }
     int best_c = 2;  // the default split
     for (int c = 0; c < 6; ++c)
-      if (p->tune_psi_us[c] > 0.0 && p->tune_psi_us[c] < 0.99 * p->tune_psi_us[best_c]) best_c = c;
+      if (dlmpc::replaces(p->tune_psi_us[c], p->tune_psi_us[best_c])) best_c = c;
     if ((rc = p->beng->set_variant(ntw, caps[best_c], err))) return fail(rc, err);
     if ((rc = p->beng->build_global(err))) return fail(rc, err);
     if (!p->beng->global_available()) return DLMPC_OK;
@@ -371,7 +371,7 @@ int tune_batch(dlmpc_problem *p) {
       if ((rc = time_k(k, &t))) return rc;
       sum += t;
     }
-    if (sum > dense && (rc = p->beng->set_global(false, err))) return fail(rc, err);
+    if (!dlmpc::replaces(sum, dense) && (rc = p->beng->set_global(false, err))) return fail(rc, err);
     return DLMPC_OK;
   };
   const int rc = run();
@@ -638,11 +638,11 @@ int choose_schedule(dlmpc_problem *p) {
   }
   int best = 0;
   double best_us = p->tune_graph_us;
-  if (can_persist && p->tune_persistent_us < best_us) {
+  if (can_persist && dlmpc::replaces(p->tune_persistent_us, best_us)) {
     best = 1;
     best_us = p->tune_persistent_us;
   }
-  if (p->struct_ok && p->tune_structured_us < best_us) {
+  if (p->struct_ok && dlmpc::replaces(p->tune_structured_us, best_us)) {
     best = 2;
     best_us = p->tune_structured_us;
   }
@@ -655,7 +655,7 @@ int choose_schedule(dlmpc_problem *p) {
     double t = 0.0;
     if ((rc = time_compact(p, m, &t))) return rc;
     if (*tune[m] <= 0.0 || t < *tune[m]) *tune[m] = t;
-    if (t < best_us) {
+    if (dlmpc::replaces(t, best_us)) {
       best_us = t;
       p->compact = m;
     }
