@@ -939,7 +939,6 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(4)
 // decision of one instance each from the residuals of every column subsystem; the last one to
 // finish publishes the iteration count and the all-stopped flag (set-up passes: none).
 __global__ __launch_bounds__(256) void bgather_kernel(BArgs a) {
-  if (a.ctl->stop) return;
   extern __shared__ __align__(16) float g_lds[];
   const int tid = threadIdx.x, B = a.ctl->batch, N = a.N;
   if (int(blockIdx.x) < N) {
@@ -947,8 +946,11 @@ __global__ __launch_bounds__(256) void bgather_kernel(BArgs a) {
     const int64_t q0 = a.rt_ptr[m];
     const int pm = int(a.rt_ptr[m + 1] - q0);
     __shared__ int64_t s_t[kMaxPatch];
+    __shared__ int s_stop;  // one read for the block: the launch's decisions may set it meanwhile
+    if (tid == 0) s_stop = a.ctl->stop;
     if (tid < pm) s_t[tid] = a.rt_tile[q0 + tid] * nuT * a.Bw;
     __syncthreads();
+    if (s_stop) return;
     for (int e = tid; e < nuT * B4; e += 256) {
       const int i = e / B4, b4 = e - i * B4;
       const float *src = a.upart + int64_t(i) * a.Bw + 4 * b4;
@@ -972,7 +974,7 @@ __global__ __launch_bounds__(256) void bgather_kernel(BArgs a) {
     }
     return;
   }
-  if (a.init_pass) return;
+  if (a.init_pass || a.ctl->stop) return;  // (set after every deciding block has read it)
   const int b = blockIdx.x - N;
   if (b >= B) return;
   __shared__ double rm[2][4];

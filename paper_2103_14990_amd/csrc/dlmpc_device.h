@@ -38,6 +38,7 @@ struct Ctl {
   int32_t inner_iters;  // single-instance engine: nested-ADMM iterations of the solve (couplings)
   uint32_t n_stop;      // batched engine: stopped instances counted by the current decision pass
   int32_t c_phi, c_psi;  // compact single solves: the iteration in progress, the latest finished one
+  int32_t c_halt;        // ... and `stop` as of an earlier launch (read where a launch also decides)
 };
 
 // Static work lists of the persistent schedule: block b runs Phi-comp for

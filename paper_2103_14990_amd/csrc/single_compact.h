@@ -110,6 +110,11 @@ __device__ __forceinline__ void cresiduals(const KArgs<Tf> &a, const CArgs<Tf> &
 
 // The decision of the latest finished iteration (c_psi), if it is still open; one block. With
 // `advance` it also opens iteration c_psi + 1 for the products that follow.
+// crow_kernel and csim_fwd_kernel decide in a block beside the ones that work, so `stop` can change
+// under those: all of their blocks go by c_halt instead, which only cstep_kernel and
+// cdecide_kernel write, in launches whose blocks do not read it. The launch that decides so always
+// runs in full (its rows are of the iteration after the stop: planes that nothing reads), and the
+// waves of a block agree at every barrier.
 template <typename Tf, int NX>
 __device__ __forceinline__ void cdecide(const KArgs<Tf> &a, const CArgs<Tf> &c, bool advance) {
   __shared__ double rp_s[16], rd_s[16];
@@ -142,8 +147,9 @@ __device__ __forceinline__ void cdecide(const KArgs<Tf> &a, const CArgs<Tf> &c, 
 
 template <typename Tf, int NX>
 __global__ __launch_bounds__(kCSimThreads) void cdecide_kernel(KArgs<Tf> a, CArgs<Tf> c) {
-  if (a.ctl->stop) return;
+  if (a.ctl->stop) return;  // (published by a cstep_kernel since)
   cdecide<Tf, NX>(a, c, false);
+  if (threadIdx.x == 0) a.ctl->c_halt = a.ctl->stop;  // its own write
 }
 
 // Per row subsystem m: x0, ||x0_m||^2, ||x_r||^2 and the rows of b that the iteration reads;
@@ -194,6 +200,7 @@ __global__ __launch_bounds__(kBlock) void cprep_kernel(KArgs<Tf> a, CArgs<Tf> c,
     k->bar_fail = 0u;
     k->c_phi = 0;
     k->c_psi = 0;
+    k->c_halt = 0;
   }
 }
 
@@ -214,7 +221,7 @@ __device__ __forceinline__ Tf crow_solve(Tf av, Tf n, Tf rho, Tf w, Tf lo, Tf hi
 // Bound by its chain of loads (list, shares): the shares are 1 / kP1Cols of the bases' bytes.
 template <typename Tf, int NX>
 __global__ __launch_bounds__(kCRowThreads) void crow_kernel(KArgs<Tf> a, CArgs<Tf> c) {
-  if (a.ctl->stop) return;
+  if (a.ctl->c_halt) return;
   if (blockIdx.x == unsigned(a.N)) {
     cdecide<Tf, NX>(a, c, true);
     return;
@@ -309,7 +316,10 @@ __device__ __forceinline__ Tf wave_sum8(const Tf *x, int lane) {
 // 56 + 41 and 94 + 66 us.
 template <typename Tf, int NX>
 __global__ __launch_bounds__(kBlock) void cstep_kernel(KArgs<Tf> a, CArgs<Tf> c) {
-  if (a.ctl->stop) return;
+  if (a.ctl->stop) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->c_halt = 1;  // read by no block of this launch
+    return;
+  }
   using V = typename VecT<Tf>::type;
   constexpr int VN = VecT<Tf>::N;
   constexpr int kUC = 8, Q = kCStepRegs;
@@ -500,7 +510,7 @@ struct CEll {  // a thread's state rows r = tid + i blockDim of A or A', first e
 // off that chain. 1024 threads: 512 with twice the registers and no spills took 47 against 29 us.
 template <typename Tf, int NX, int RPT, int KU, int BD>
 __global__ __launch_bounds__(BD) void csim_fwd_kernel(KArgs<Tf> a, CArgs<Tf> c) {
-  if (a.ctl->stop) return;
+  if (a.ctl->c_halt) return;
   if (int(blockIdx.x) == kCParts) {
     cdecide<Tf, NX>(a, c, true);
     return;
