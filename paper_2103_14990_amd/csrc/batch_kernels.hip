@@ -95,15 +95,9 @@ __device__ __forceinline__ T wsum(T v) {
   return v;
 }
 
-// Element (b, m, l) of the row vectors alpha and s, and the subsystem and local row of their e-th
-// element in storage order (instances aside).
+// Element (b, m, l) of the row vectors alpha and s.
 __device__ __forceinline__ int64_t row_at(const BArgs &a, int b, int m, int l) {
   return b * a.rb + m * a.rm + l * a.rl;
-}
-__device__ __forceinline__ void row_decode(const BArgs &a, int64_t e, int &m, int &l) {
-  const int d = a.glob ? a.N : a.rs, q = int(e / d), r = int(e - int64_t(q) * d);
-  m = a.glob ? r : q;
-  l = a.glob ? q : r;
 }
 
 #include "batch_global.h"
@@ -938,11 +932,16 @@ __global__ __launch_bounds__(256) void boutput_kernel(BArgs a, double *u0, const
   const int64_t ny = int64_t(a.N) * a.rs, chunk = (ny + kParts - 1) / kParts;
   const int64_t r0 = part * chunk, r1 = min(ny, r0 + chunk);
   double acc = 0.0;
-  for (int64_t i = r0 + tid; i < r1; i += 256) {
-    int m, l;
-    row_decode(a, i, m, l);
-    const double y = double(a.s[row_at(a, b, m, l)]);
-    acc += a.w64[int64_t(m) * a.rs + l] * y * y;
+  if (a.glob) {  // rows in storage order: l N + m (row counts fit in 32 bits there)
+    const float *sb = a.s + b * a.rb;
+    for (int i = int(r0) + tid; i < int(r1); i += 256) {
+      const int l = i / a.N, m = i - l * a.N;
+      const double y = double(sb[i]);
+      acc += a.w64[int64_t(m) * a.rs + l] * y * y;
+    }
+  } else {
+    const float *sb = a.s + b;  // row i of instance b at sb[i * Bmax]
+    for (int64_t i = r0 + tid; i < r1; i += 256) acc += a.w64[i] * double(sb[i * a.Bmax]) * double(sb[i * a.Bmax]);
   }
   acc = wsum(acc);
   if ((tid & 63) == 0) red[tid >> 6] = acc;
