@@ -684,13 +684,14 @@ bool finite_all(const float *v, size_t n) {
   return true;
 }
 
-// The solve loop shared by the host- and device-buffer entry points. x0_dev, u0_dev on device.
+// The solve loop shared by the host- and device-buffer entry points. x0_dev, u0_dev on device;
+// `standard`: not in the compact form.
 int run_solve(dlmpc_problem *p, const double *x0_dev, const double *wpsi, const double *wlam,
-              double *u0_dev, double *phi_dev, dlmpc_stats *stats, double t_host0_ms) {
+              double *u0_dev, double *phi_dev, dlmpc_stats *stats, double t_host0_ms, bool standard = false) {
   std::string err;
   const int max_iter = p->opt.max_iter;
   // cold starts without couplings: the compact form where setup chose it
-  const int compact = !wpsi && p->cp_a.empty() ? p->compact : 0;
+  const int compact = !standard && !wpsi && p->cp_a.empty() ? p->compact : 0;
   const int sched = compact ? (compact == dlmpc::kCompactBlock ? 1 : 0) : p->sched;
   hipGraphExec_t *exec = compact ? p->cgexec : p->gexec;
   API_HIP(hipEventRecord(p->ev_p0, p->stream));
@@ -759,6 +760,9 @@ int run_solve(dlmpc_problem *p, const double *x0_dev, const double *wpsi, const 
   API_HIP(hipMemcpyAsync(&p->h_ctl[0], d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost, p->stream));
   API_HIP(hipStreamSynchronize(p->stream));
   const Ctl &c = p->h_ctl[0];
+  // Where squares of x0 leave the range of the type (past 1e19 in FP32, 1e154 in FP64) the compact
+  // residuals, xc^2 times a sum, are NaN while the standard form's columns can still be finite.
+  if (compact && c.numeric) return run_solve(p, x0_dev, wpsi, wlam, u0_dev, phi_dev, stats, t_host0_ms, true);
   // FP64 certificate of the stopping iterate (synchronises)
   double cert[5] = {0, 0, 0, 0, 0};
   float mc = 0.f;
