@@ -39,9 +39,11 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 CSRC = os.path.join(ROOT, "paper_2103_14990_amd", "csrc")
-# kernels behind the three timed launches when the engine iterates through the global recursions
+# kernels behind the three timed launches when the engine iterates through the global recursions, and
+# when both recursions of an instance run in one kernel
 GLOBAL_KERNELS = {"bphi_kernel": "bsim_fwd_kernel", "bpsi_kernel": "bsim_adj_kernel + bstep_kernel",
                   "bdecide_kernel": "bgather_kernel"}
+FUSED_KERNELS = {"bphi_kernel": "bsim_both_kernel", "bpsi_kernel": "bstep_kernel", "bdecide_kernel": "bgather_kernel"}
 
 
 def log(*a):
@@ -63,6 +65,12 @@ def kernel_source_hash(kernel: str) -> str:
     return hashlib.sha256(src[start:end if end > 0 else len(src)].encode()).hexdigest()[:16]
 
 
+def recursions_fused(n_sub: int, nx: int, rs: int) -> bool:
+    """Whether the global recursions of an instance run in one kernel (the sizes that
+    dlmpc_time_batch_kernels states in include/dlmpc.h)."""
+    return n_sub <= 1024 and n_sub * nx <= 2048 and n_sub * rs <= 16384
+
+
 def batch_algorithmic_bytes(info: dict, n_sub: int, rs: int, B: int, basis_bytes: int = 4) -> dict:
     """Bytes each batched kernel must move per launch for B instances (lower bound: every
     array touched once). The null bases are stored as bf16 hi + lo (4 B per entry; 2 B in the
@@ -73,7 +81,8 @@ def batch_algorithmic_bytes(info: dict, n_sub: int, rs: int, B: int, basis_bytes
     Through the global recursions (info batch_global): the first launch reads alpha_prev, the input
     rows of b and U, writes alpha and s; the second reads alpha and the input rows of the bases once,
     tau and eta (read, write), g (write, read), writes every tile's share of U; the third reads the
-    shares and writes U.
+    shares and writes U. With both recursions in one kernel (info recursions_fused) the first launch
+    writes g, and alpha is not read again.
     """
     dk, sk, R = info["sum_dcol_k"], info["sum_k"], n_sub * rs
     if info["batch_global"] and basis_bytes == 4:
@@ -82,6 +91,9 @@ def batch_algorithmic_bytes(info: dict, n_sub: int, rs: int, B: int, basis_bytes
         fwd = 12 * B * R + 12 * R + 8 * B * n_sub * nu_t
         step = 4 * B * R + 4 * info["sum_du_k"] + 16 * B * sk + 8 * B * n_sub * nu_t + share
         gather = share + 4 * B * n_sub * nu_t
+        if info["recursions_fused"]:
+            fwd += 4 * B * n_sub * nu_t
+            step -= 4 * B * R + 4 * B * n_sub * nu_t
         return {"bphi_kernel": fwd, "bpsi_kernel": step, "bdecide_kernel": gather, "iteration": fwd + step + gather}
     nb = basis_bytes * dk
     bpsi = nb + 4 * B * R + 16 * B * sk + 4 * B * sk + 8 * B * n_sub
@@ -791,14 +803,16 @@ def main() -> int:
 
     # ---- roofline of the dominant batched kernel (HIP events around each launch)
     glob = bool(pr.info["batch_global"])
-    ab = batch_algorithmic_bytes({**pr.info, "input_rows": net.nu * (wl.T - 1)}, N, rs, B)
+    fused = glob and recursions_fused(N, net.nx, rs)
+    ab = batch_algorithmic_bytes({**pr.info, "input_rows": net.nu * (wl.T - 1), "recursions_fused": fused}, N, rs, B)
+    names = FUSED_KERNELS if fused else GLOBAL_KERNELS
     ku = pr.time_batch_kernels(B, x0[args.warmup].data_ptr(), 20)
     kname = max(ku, key=ku.get)
-    per_kernel = {GLOBAL_KERNELS[k] if glob else k:
+    per_kernel = {names[k] if glob else k:
                   {"us": round(v, 2), "GB/s": round(ab[k] / (v * 1e-6) / 1e9, 1) if ab[k] else None}
                   for k, v in ku.items()}
     achieved = ab[kname] / (ku[kname] * 1e-6) / 1e9
-    kshow = GLOBAL_KERNELS[kname] if glob else kname
+    kshow = names[kname] if glob else kname
     roofline = {"bound": "hbm", "kernel": kshow, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "avg_launch_us": round(ku[kname], 2), "algorithmic_bytes_per_launch": int(ab[kname]),

@@ -340,7 +340,9 @@ int dlmpc_time_kernels(struct dlmpc_problem *p, const double *x0_dev, int32_t it
  * the global recursions (dlmpc_info.batch_global): the forward recursion with the row update
  * (bsim_fwd_kernel); the adjoint recursion and the products with the input rows, with Lambda and
  * Conv terms (bsim_adj_kernel + bstep_kernel); the sum of the products and the stopping decision
- * (bgather_kernel). With the dense products: the batched Phi-comp
+ * (bgather_kernel). On networks of at most 1024 subsystems, 2048 states and N (nx T + nu (T - 1)) =
+ * 16384 rows one kernel runs both recursions of an instance: the first step is then both recursions
+ * with the row update (bsim_both_kernel) and the second the products alone. With the dense products: the batched Phi-comp
  * (bphi_kernel: row solves of all instances, products with the null bases on the matrix
  * cores), the batched Psi-comp with Lambda and Conv terms (bpsi_kernel) and the per-instance
  * stopping decision (bdecide_kernel). The batched state is left unspecified. */

@@ -343,8 +343,9 @@ class BatchEngine {
   virtual bool global_available() const = 0;
   virtual int set_global(bool on, std::string &err) = 0;
   virtual bool global_on() const = 0;
-  // One kernel of an iteration: 0 bphi_kernel, 1 bpsi_kernel, 2 bdecide_kernel (global recursions:
-  // 0 bsim_fwd_kernel, 1 bsim_adj_kernel and bstep_kernel, 2 bgather_kernel).
+  // One step of an iteration: 0 bphi_kernel, 1 bpsi_kernel, 2 bdecide_kernel (global recursions:
+  // 0 bsim_fwd_kernel, 1 bsim_adj_kernel and bstep_kernel, 2 bgather_kernel; where one kernel runs both
+  // recursions, 0 bsim_both_kernel, 1 bstep_kernel).
   virtual int launch_one(int k, std::string &err) = 0;
   virtual int output(double *u0_dev, std::string &err) = 0;
   // Base penalty of the solves started after this call (per-instance factors multiply it).
