@@ -2144,7 +2144,7 @@ class EngineT final : public Engine {
     return DLMPC_OK;
   }
   static constexpr size_t kCSolveLds = 150 * 1024;
-  static constexpr size_t kCStepLds = 44 * 1024;  // one patch's rows, beside the shares' 16 KB
+  static constexpr size_t kCStepLds = 44 * 1024;  // one patch's rows, beside the shares' 8 KB
   CArgs<Tf> cd_{}, cg_{};
   CSolveLds csolve_{};
   size_t cstep_lds_[2] = {0, 0};

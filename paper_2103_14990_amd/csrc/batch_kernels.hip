@@ -2551,9 +2551,13 @@ class BatchEngineT final : public BatchEngine {
       default: return go(bsim_adj_kernel<NX, 4>);
     }
   }
-  // Largest instance that takes bsim_both_kernel: at 30 KB (16 x 16 grid, T = 10, 64 instances) one
-  // block replaces 4 + 1 and wins, at 93 KB (667 nodes, T = 12, 23 instances: 11 + 1 blocks) the two
-  // are equal, 38 against 39 us, as the row update of one CU grows; past it the parts win.
+  // Largest instance that takes bsim_both_kernel (bench.py and dlmpc.h state the resulting sizes). One
+  // block per instance saves a launch and alpha's way through memory; the two kernels share the row
+  // update over up to eight blocks per instance. Whole iterations in us, two kernels / one, at 2, 23
+  // and 64 instances: 29 KB (16 x 16 grid, T = 10) 42.0 / 39.0, 48.8 / 44.5, 55.2 / 51.6; 56 KB (chain
+  // of 1024, T = 5) 52.6 / 50.5, 59.7 / 55.0, 80.0 / 75.8; 62 KB (19 x 19, T = 15) 56.8 / 57.6, 64.3 /
+  // 64.7, 79.9 / 79.4; 69 KB (20 x 20, T = 15) 57.4 / 60.0, 65.7 / 67.6, 83.7 / 84.2; 91 KB (mesh of 667,
+  // T = 12) 68.5 / 69.5, 80.9 / 79.7, 100.0 / 97.5; 135 KB 85.8 / 90.6, 102.0 / 104.5, 133.6 / 135.0.
   static constexpr size_t kSimBothLds = 64 * 1024;
   void launch_both(const BArgs &x) {
     const int NS = hs_->N * NX;  // a thread per state row, and per four rows of the update
