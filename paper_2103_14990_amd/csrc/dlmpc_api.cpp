@@ -661,6 +661,12 @@ int choose_schedule(dlmpc_problem *p) {
     }
   }
   p->eng->settle(p->compact, best == 2);
+  for (int g = 0; g < dlmpc_problem::kGraphs; ++g) {  // of the form timed last
+    if (p->cgexec[g]) (void)hipGraphExecDestroy(p->cgexec[g]);
+    if (p->cgraph[g]) (void)hipGraphDestroy(p->cgraph[g]);
+    p->cgexec[g] = nullptr;
+    p->cgraph[g] = nullptr;
+  }
   if ((p->compact == dlmpc::kCompactDense || p->compact == dlmpc::kCompactGlobal) &&
       (rc = capture_compact(p, p->compact)))
     return rc;
