@@ -235,7 +235,7 @@ typedef struct {
    * couplings always run the standard form) and the batched engine's kernel variants are chosen by timing at setup, or taken
    * from the cache file named by the environment variable DLMPC_TUNE_CACHE (one line per problem
    * signature: sizes, precision, max_batch and the device's architecture; appended after a timed
-   * setup). Batched variants: instance tiles per Phi-comp wave (1: each basis fragment feeds one
+   * setup; a line written before one of these forms existed goes on without it). Batched variants: instance tiles per Phi-comp wave (1: each basis fragment feeds one
    * 16-instance tile; 2: two, with half the waves loading it), and the split of heavy column blocks
    * over several Psi-comp work units (the waves serving one patch): a block whose basis cost
    * exceeds batch_psi_capx times the mean is split. */

@@ -2083,8 +2083,9 @@ class EngineT final : public Engine {
     return *modes ? compact_lists(cd_, rs, hs.nb_off, cdmem_, err) : DLMPC_OK;
   }
 
-  // Global recursions: states of one step on chip, and a plant that does not amplify (FP64
-  // has the digits to spare: its limit is the growth that costs six of them).
+  // Global recursions: states of one step on chip, and a plant that does not amplify (FP64 has the
+  // digits to spare: at a growth of 668 over the horizon u(0) and Phi of random plants are as close
+  // to the oracle as through the whole bases, 1.6e-12 and 5.0e-12 relative).
   int build_compact_global(int *modes, std::string &err) {
     const HostSetup &hs = *hs_;
     const int N = hs.N, NS = N * NX, nuT = hs.nu * (hs.T - 1), rs = hs.rs;

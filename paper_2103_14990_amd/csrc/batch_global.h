@@ -20,7 +20,7 @@
 // 267, bdecide 8), 253 us here (32 + 27 + 174 + 20); 64 of the 16 x 16 boxed grid 63 -> 43 us.
 // The recursions run in FP32; products accumulate over fewer rows, so the iterate is closer to
 // the FP64 one than through the dense bases (u(0) after 50 iterations on the 16 x 16 boxed grid:
-// 6e-7 against 2e-6 relative). A plant whose A^t grows over the horizon amplifies the rounding of
+// 4.8e-7 against 2.1e-6 relative). A plant whose A^t grows over the horizon amplifies the rounding of
 // U in x; such plants keep the dense products (see kMaxGrowth in batch_kernels.hip).
 #pragma once
 

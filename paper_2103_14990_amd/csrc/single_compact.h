@@ -17,7 +17,7 @@
 // The iterates are those of the standard form up to rounding: same counts in FP64.
 // Measured, us per iteration, the standard form's best schedule -> here: 10-node chain FP64 (d = 1,
 // T = 5) 14.6 -> 4.3 (one workgroup); paper's chain of 100 FP64 23.3 -> 11.4 (whole bases: crow 4.8 +
-// cstep 6.7); 1024-node mesh (d = 3, T = 15) FP64 255 -> 147 and FP32 146 -> 84 (input rows: csim_fwd
+// cstep 6.7); 1024-node mesh (d = 3, T = 15) FP64 255 -> 148 and FP32 146 -> 85 (input rows: csim_fwd
 // 30 / 24, csim_adj 28 / 19, cstep 81 / 36, crow 9 / 8; whole bases: 315 and 151).
 // Which form a problem uses is chosen by timing at setup: whole bases win where the two
 // recursions' 2 T dependent steps cost more than the state rows' bytes, one workgroup where a
