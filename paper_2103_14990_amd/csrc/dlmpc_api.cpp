@@ -306,65 +306,10 @@ void tune_cache_write(const std::string &sig, int phi_ntw, int psi_capx, int sch
   std::fclose(f);
 }
 
-// Iterations that setup times a form over: graphs of 2^g iterations, the forms of one launch 2^(g+1).
-// Eight iterations of the smallest networks take 40 us and more, as long as two of the bases of 256 MB.
-int timed_graph(const dlmpc_problem *p) {
-  const double bytes = double(p->hs.sum_dcol_k) * (p->opt.precision == DLMPC_FP64 ? 8 : 4);
-  return bytes >= 256e6 ? 1 : 3;
-}
-
-// Time of what run enqueues after start: the least of up to three samples, fewer where they are long
-// (a single sample of 0.2 ms was seen off by more than the 15 % between two forms; twice 32
-// iterations of every form, as once, were 121 of the 217 ms of setup on the 1024-node mesh in FP64).
-template <class Start, class Run>
-int time_samples(dlmpc_problem *p, Start start, Run run, double *us) {
-  double sum = 0.0;
-  *us = 1e30;
-  for (int k = 0; k < 3 && sum < 1e3; ++k) {
-    int rc = start();
-    if (rc) return rc;
-    API_HIP(hipEventRecord(p->ev_t0, p->stream));
-    if ((rc = run())) return rc;
-    API_HIP(hipEventRecord(p->ev_t1, p->stream));
-    API_HIP(hipEventSynchronize(p->ev_t1));
-    float ms = 0.f;
-    API_HIP(hipEventElapsedTime(&ms, p->ev_t0, p->ev_t1));
-    *us = std::min(*us, 1e3 * double(ms));
-    sum += 1e3 * double(ms);
-  }
-  return DLMPC_OK;
-}
-
-// (Re)captures the batched iteration's graph of 2^g iterations (with the CG steps of streamed joins).
-int capture_batch(dlmpc_problem *p, int joins, int g) {
-  std::string err;
-  hipGraph_t &gr = joins ? p->sgraph[g] : p->bgraph[g];
-  hipGraphExec_t &ex = joins ? p->sgexec[g] : p->bgexec[g];
-  if (ex) (void)hipGraphExecDestroy(ex);
-  if (gr) (void)hipGraphDestroy(gr);
-  ex = nullptr;
-  gr = nullptr;
-  API_HIP(hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
-  for (int i = 0; i < (1 << g); ++i) {
-    const int rc = p->beng->iteration(err, joins != 0);
-    if (rc) {
-      hipGraph_t q = nullptr;
-      (void)hipStreamEndCapture(p->stream, &q);
-      if (q) (void)hipGraphDestroy(q);
-      return fail(rc, err);
-    }
-  }
-  API_HIP(hipStreamEndCapture(p->stream, &gr));
-  API_HIP(hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0));
-  return DLMPC_OK;
-}
-
 // Times the batched-engine variants with max_batch instances from a zero-multiplier start (every
 // launch does the full work; x0 = 1 everywhere) and keeps the fastest Phi-comp and Psi-comp; then
-// the iteration through the global recursions against the one through the chosen dense variants
-// (dlmpc::replaces), both as captured iterations. (Launches timed one by one carry some 4 us each that
-// hide what a graph gives back: chain of 22, one instance, 31.7 us each way one by one, solves of
-// 32 iterations 763 us through the dense products and 827 us through the recursions.)
+// the iteration through the global recursions, kept when its launches take less time than those
+// of the chosen dense variants (dlmpc::replaces).
 int tune_batch(dlmpc_problem *p) {
   const HostSetup &hs = p->hs;
   const int B = p->beng->bmax();
@@ -382,7 +327,7 @@ int tune_batch(dlmpc_problem *p) {
     if (rc) return fail(rc, err);
     auto time_k = [&](int k, double *us) -> int {
       float best = 1e30f;
-      for (int rep = 0; rep < 4; ++rep) {  // the first launch warms code and caches
+      for (int rep = 0; rep < 6; ++rep) {  // the first launch warms code and caches
         API_HIP(hipEventRecord(p->ev_t0, p->stream));
         int r = p->beng->launch_one(k, err);
         if (r) return fail(r, err);
@@ -415,22 +360,18 @@ int tune_batch(dlmpc_problem *p) {
     if ((rc = p->beng->set_variant(ntw, caps[best_c], err))) return fail(rc, err);
     if ((rc = p->beng->build_global(err))) return fail(rc, err);
     if (!p->beng->global_available()) return DLMPC_OK;
-    double us[2] = {0.0, 0.0};  // dense products, global recursions
-    const int g = timed_graph(p);
-    for (int glob = 0; glob < 2; ++glob) {
-      if ((rc = p->beng->set_global(glob != 0, err))) return fail(rc, err);
-      rc = p->beng->precompute(x, B, 1 << 20, -1.0, 1, nullptr, err);
-      if (!rc) rc = p->beng->start_alpha(z, err);
-      if (rc) return fail(rc, err);
-      if ((rc = capture_batch(p, 0, g))) return rc;
-      auto launch = [&]() -> int {
-        API_HIP(hipGraphLaunch(p->bgexec[g], p->stream));
-        return DLMPC_OK;
-      };
-      if ((rc = launch())) return rc;  // warms code and caches
-      if ((rc = time_samples(p, [] { return DLMPC_OK; }, launch, &us[glob]))) return rc;
+    double dense = p->tune_phi_us[ntw - 1] + p->tune_psi_us[best_c], t = 0.0, sum = 0.0;
+    if ((rc = time_k(2, &t))) return rc;
+    dense += t;
+    if ((rc = p->beng->set_global(true, err))) return fail(rc, err);
+    rc = p->beng->precompute(x, B, 1 << 20, -1.0, 1, nullptr, err);
+    if (!rc) rc = p->beng->start_alpha(z, err);
+    if (rc) return fail(rc, err);
+    for (int k = 0; k < 3; ++k) {
+      if ((rc = time_k(k, &t))) return rc;
+      sum += t;
     }
-    if (!dlmpc::replaces(us[1], us[0]) && (rc = p->beng->set_global(false, err))) return fail(rc, err);
+    if (!dlmpc::replaces(sum, dense) && (rc = p->beng->set_global(false, err))) return fail(rc, err);
     return DLMPC_OK;
   };
   const int rc = run();
@@ -488,8 +429,22 @@ int setup_batch(dlmpc_problem *p) {
   }
   p->beng->settle();
   for (int joins = 0; joins < 2; ++joins)
-    for (int g = 0; g < dlmpc_problem::kGraphs; ++g)
-      if ((rc = capture_batch(p, joins, g))) return rc;
+    for (int g = 0; g < dlmpc_problem::kGraphs; ++g) {
+      API_HIP(hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
+      for (int i = 0; i < (1 << g); ++i) {
+        rc = p->beng->iteration(err, joins != 0);
+        if (rc) {
+          hipGraph_t gr = nullptr;
+          (void)hipStreamEndCapture(p->stream, &gr);
+          if (gr) (void)hipGraphDestroy(gr);
+          return fail(rc, err);
+        }
+      }
+      hipGraph_t &gr = joins ? p->sgraph[g] : p->bgraph[g];
+      hipGraphExec_t &ex = joins ? p->sgexec[g] : p->bgexec[g];
+      API_HIP(hipStreamEndCapture(p->stream, &gr));
+      API_HIP(hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0));
+    }
   API_HIP(hipStreamSynchronize(p->stream));
   return DLMPC_OK;
 }
@@ -541,6 +496,16 @@ struct ChunkPredictor {
   }
 };
 
+// Iterations that setup times a form over: graphs of 2^g iterations, one of them to warm code and
+// caches and one timed; the forms of one launch over 2^(g+1), after a few. 16 iterations of the
+// smallest networks take 70 us and more; where the bases have 256 MB an iteration takes 80 us and
+// more, and four tell the forms apart. (Twice 32 iterations each, as before: 121 of the 217 ms that
+// setup took on the 1024-node mesh in FP64.)
+int timed_graph(const dlmpc_problem *p) {
+  const double bytes = double(p->hs.sum_dcol_k) * (p->opt.precision == DLMPC_FP64 ? 8 : 4);
+  return bytes >= 256e6 ? 2 : 4;
+}
+
 // Times a form of the single solve (run enqueues n iterations after start) from x0 = (1, ..., 1) with
 // the stop test disabled.
 template <class Start, class Run>
@@ -548,11 +513,18 @@ int time_form(dlmpc_problem *p, int warm, int n, Start start, Run run, double *u
   const HostSetup &hs = p->hs;
   std::vector<double> ones(size_t(hs.N) * hs.nx, 1.0);
   API_HIP(hipMemcpy(p->d_x0, ones.data(), ones.size() * sizeof(double), hipMemcpyHostToDevice));
-  int rc = start(warm);  // warms code and caches
-  if (!rc) rc = run(warm);
-  if (!rc) rc = time_samples(p, [&] { return start(n); }, [&] { return run(n); }, us_per_iter);
-  *us_per_iter /= n;
-  return rc;
+  for (int k : {warm, n}) {
+    int rc = start(k);
+    if (rc) return rc;
+    API_HIP(hipEventRecord(p->ev_t0, p->stream));
+    if ((rc = run(k))) return rc;
+    API_HIP(hipEventRecord(p->ev_t1, p->stream));
+    API_HIP(hipStreamSynchronize(p->stream));
+  }
+  float ms = 0.f;
+  API_HIP(hipEventElapsedTime(&ms, p->ev_t0, p->ev_t1));
+  *us_per_iter = 1e3 * double(ms) / n;
+  return DLMPC_OK;
 }
 
 // A schedule of the standard form: 0 graph (captures the graph that it times), 1 persistent.
@@ -562,7 +534,7 @@ int time_schedule(dlmpc_problem *p, int sched, double *us_per_iter) {
   int rc = sched == 1 ? DLMPC_OK : capture_single(p, g, g + 1);
   if (rc) return rc;
   rc = time_form(
-      p, sched == 1 ? std::max(1, n / 8) : n, n,
+      p, sched == 1 ? n / 8 : n, n,
       [&](int k) {
         const int r = p->eng->precompute(p->d_x0, nullptr, nullptr, k, -1.0, p->opt.rho, err);
         return r ? fail(r, err) : DLMPC_OK;
@@ -587,7 +559,7 @@ int time_compact(dlmpc_problem *p, int mode, double *us_per_iter) {
   const int rc = one ? DLMPC_OK : capture_compact(p, mode, g, g + 1);
   if (rc) return rc;
   return time_form(
-      p, one ? std::max(1, n / 8) : n, n,
+      p, one ? n / 8 : n, n,
       [&](int k) {
         const int r = p->eng->compact_precompute(mode, p->d_x0, k, -1.0, p->opt.rho, err);
         return r ? fail(r, err) : DLMPC_OK;

@@ -26,9 +26,9 @@ def test_margin(tmp_path, us, kept, want):
 
 
 def test_every_choice_uses_the_rule():
-    """Timings (tune_*_us, captured batched iterations, a compact form's time) are compared by it alone."""
+    """Timings (tune_*_us, the sums of launches, a compact form's time) are compared by it alone."""
     src = open(os.path.join(CSRC, "dlmpc_api.cpp")).read()
     body = src[src.index("int tune_batch("):src.rindex("int setup_batch(")] + \
         src[src.index("int choose_schedule(dlmpc_problem *p) {"):src.index("bool finite_all(")]
     assert len(re.findall(r"dlmpc::replaces\(", body)) == 6
-    assert not re.search(r"(tune_\w+_us(\[\w+\])?|\bus(\[\w\])?|\bt) *[<>] *(0\.99|best_us|dense|p->tune)", body)
+    assert not re.search(r"(tune_\w+_us(\[\w+\])?|\bsum|\bt) *[<>] *(0\.99|best_us|dense|p->tune)", body)
