@@ -308,8 +308,12 @@ void tune_cache_write(const std::string &sig, int phi_ntw, int psi_capx, int sch
 
 // Times the batched-engine variants with max_batch instances from a zero-multiplier start (every
 // launch does the full work; x0 = 1 everywhere) and keeps the fastest Phi-comp and Psi-comp; then
-// the iteration through the global recursions, kept when its launches take less time than those
-// of the chosen dense variants (dlmpc::replaces).
+// the iteration through the global recursions, kept unless the launches of the chosen dense
+// variants take less time (dlmpc::replaces): near-ties go to the form whose u(0) is the closer to
+// 64 bits (chains and grids of 10 to 64 nodes: 1e-7 against 1e-6). Launches timed one by one carry
+// some 4 us each that a captured iteration does not: on the smallest networks, where the sums are
+// near-ties, solves through the dense products take up to 12 % less time (chain of 22, one
+// instance, 32 iterations: 763 against 827 us, error 10 times as large).
 int tune_batch(dlmpc_problem *p) {
   const HostSetup &hs = p->hs;
   const int B = p->beng->bmax();
@@ -371,7 +375,7 @@ int tune_batch(dlmpc_problem *p) {
       if ((rc = time_k(k, &t))) return rc;
       sum += t;
     }
-    if (!dlmpc::replaces(sum, dense) && (rc = p->beng->set_global(false, err))) return fail(rc, err);
+    if (dlmpc::replaces(dense, sum) && (rc = p->beng->set_global(false, err))) return fail(rc, err);
     return DLMPC_OK;
   };
   const int rc = run();
@@ -496,34 +500,39 @@ struct ChunkPredictor {
   }
 };
 
-// Iterations that setup times a form over: graphs of 2^g iterations, one of them to warm code and
-// caches and one timed; the forms of one launch over 2^(g+1), after a few. 16 iterations of the
-// smallest networks take 70 us and more; where the bases have 256 MB an iteration takes 80 us and
-// more, and four tell the forms apart. (Twice 32 iterations each, as before: 121 of the 217 ms that
-// setup took on the 1024-node mesh in FP64.)
+// Iterations that setup times a form of single solves over: graphs of 2^g iterations, the forms of one
+// launch 2^(g+1). Eight iterations of the smallest networks take 40 us and more, as long as two of the
+// bases of 256 MB. (Twice 32 iterations each, as once: 121 of the 217 ms that setup took on the
+// 1024-node mesh in FP64.)
 int timed_graph(const dlmpc_problem *p) {
   const double bytes = double(p->hs.sum_dcol_k) * (p->opt.precision == DLMPC_FP64 ? 8 : 4);
-  return bytes >= 256e6 ? 2 : 4;
+  return bytes >= 256e6 ? 1 : 3;
 }
 
 // Times a form of the single solve (run enqueues n iterations after start) from x0 = (1, ..., 1) with
-// the stop test disabled.
+// the stop test disabled: the least of up to three samples, fewer where they are long (single
+// samples of 0.2 ms were seen off by more than 15 %).
 template <class Start, class Run>
 int time_form(dlmpc_problem *p, int warm, int n, Start start, Run run, double *us_per_iter) {
   const HostSetup &hs = p->hs;
   std::vector<double> ones(size_t(hs.N) * hs.nx, 1.0);
   API_HIP(hipMemcpy(p->d_x0, ones.data(), ones.size() * sizeof(double), hipMemcpyHostToDevice));
-  for (int k : {warm, n}) {
-    int rc = start(k);
-    if (rc) return rc;
+  int rc = start(warm);  // warms code and caches
+  if (!rc) rc = run(warm);
+  if (rc) return rc;
+  double best = 1e30, sum = 0.0;
+  for (int k = 0; k < 3 && sum < 1.0; ++k) {
+    if ((rc = start(n))) return rc;
     API_HIP(hipEventRecord(p->ev_t0, p->stream));
-    if ((rc = run(k))) return rc;
+    if ((rc = run(n))) return rc;
     API_HIP(hipEventRecord(p->ev_t1, p->stream));
-    API_HIP(hipStreamSynchronize(p->stream));
+    API_HIP(hipEventSynchronize(p->ev_t1));
+    float ms = 0.f;
+    API_HIP(hipEventElapsedTime(&ms, p->ev_t0, p->ev_t1));
+    best = std::min(best, double(ms));
+    sum += double(ms);
   }
-  float ms = 0.f;
-  API_HIP(hipEventElapsedTime(&ms, p->ev_t0, p->ev_t1));
-  *us_per_iter = 1e3 * double(ms) / n;
+  *us_per_iter = 1e3 * best / n;
   return DLMPC_OK;
 }
 
@@ -534,7 +543,7 @@ int time_schedule(dlmpc_problem *p, int sched, double *us_per_iter) {
   int rc = sched == 1 ? DLMPC_OK : capture_single(p, g, g + 1);
   if (rc) return rc;
   rc = time_form(
-      p, sched == 1 ? n / 8 : n, n,
+      p, sched == 1 ? std::max(1, n / 8) : n, n,
       [&](int k) {
         const int r = p->eng->precompute(p->d_x0, nullptr, nullptr, k, -1.0, p->opt.rho, err);
         return r ? fail(r, err) : DLMPC_OK;
@@ -559,7 +568,7 @@ int time_compact(dlmpc_problem *p, int mode, double *us_per_iter) {
   const int rc = one ? DLMPC_OK : capture_compact(p, mode, g, g + 1);
   if (rc) return rc;
   return time_form(
-      p, one ? n / 8 : n, n,
+      p, one ? std::max(1, n / 8) : n, n,
       [&](int k) {
         const int r = p->eng->compact_precompute(mode, p->d_x0, k, -1.0, p->opt.rho, err);
         return r ? fail(r, err) : DLMPC_OK;
